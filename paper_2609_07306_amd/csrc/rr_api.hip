@@ -25,6 +25,7 @@ struct rr_ledger {
     float *alpha, *beta;
     float *seed_bound, *seed_rmax;  // dense rescoring -> reroute: per-row threshold seeds (or null)
     bool fused;                     // relay layers as one pass (else rescoring + compacted reroute)
+    bool resident;                  // ... by the resident-score kernel
     int32_t bm_words;               // fused: ledger bitmap row stride in (R, C) word pairs
     uint32_t *done;                 // fused: finished-workgroup counter of the relay pass
     int64_t *blk_pairs;  // rescoring workgroup partials, consumed by the reroute kernel
@@ -304,6 +305,7 @@ rr::RouteArgs route_args(const rr_config &c, const void *Q, const void *K)
 // pass leaves threshold seeds.
 struct RelayPlan {
     bool fused, seeds;
+    bool resident;  // the one pass is the resident-score kernel
     int bm_words;
     rr::RescoreGeometry geo;
 };
@@ -312,9 +314,11 @@ RelayPlan relay_plan(const rr_config &c)
 {
     RelayPlan p;
     p.bm_words = relay_bm_words(c.n_k);
+    const bool split = (c.options & RR_OPT_SPLIT_RELAY) != 0;
+    p.resident = !split && rr::resident_shape(c.n_k, c.k + c.m) != 0;
     const bool fits = p.bm_words <= rr::route_relay_max_bm_words(c.dtype, c.d, c.k + c.m);
     rr::rescore_geometry(rows_of(c), c.n_q, c.n_k, p.geo);
-    p.fused = fits && ((c.options & RR_OPT_ONE_PASS_RELAY) || (!(c.options & RR_OPT_SPLIT_RELAY) && c.causal));
+    p.fused = p.resident || (fits && ((c.options & RR_OPT_ONE_PASS_RELAY) || (!split && c.causal)));
     p.seeds = !p.fused && p.geo.dense && rr::rescore_dense_seeds(c.dtype, c.d);
     return p;
 }
@@ -328,6 +332,9 @@ int64_t relay_partial_slots(const rr_config &c)
     const int64_t tiles = (int64_t)c.n_heads * ((c.n_q + tile - 1) / tile);
     return rescore > tiles ? rescore : tiles;
 }
+
+// Words of a one-pass relay's counters (RouteArgs::done), zero between launches.
+constexpr int kDoneWords = 4;
 
 // Byte offsets of the relay scratch inside the static area (each 256-byte
 // aligned) and the bytes it takes.
@@ -345,7 +352,7 @@ StaticLayout static_layout(const rr_config &c, const RelayPlan &p)
         at = (at + bytes + 255) & ~(size_t)255;
         return o;
     };
-    l.done = take(sizeof(uint32_t));
+    l.done = take(kDoneWords * sizeof(uint32_t));
     l.stat_pairs = take(sizeof(int64_t));
     l.stat_nrr = take(sizeof(int32_t));
     l.blk_pairs = take(slots * sizeof(int64_t));
@@ -371,6 +378,7 @@ struct RelayBuffers {
     int32_t *stat_nrr = nullptr;
     uint32_t *done = nullptr;  // one pass: finished-workgroup counter (zero between launches)
     bool fused = false;
+    bool resident = false;  // the one pass also writes `routes`
     int32_t bm_words = 0;
     unsigned long long *unconverged = nullptr;
 };
@@ -408,6 +416,7 @@ rr_status relay_launch(const rr_config &c, const RelayBuffers &b, int32_t layer,
         a.stat_nrr = b.stat_nrr;
         a.pairs_out = pairs;
         a.nrr_out = n_rerouted;
+        if (b.resident) a.routes_out = routes;
         const int grid = c.n_heads * a.tiles_per_head;
         hipError_t e = launch(RR_KERNEL_RELAY, [&] { return rr::launch_route(a, c.dtype, grid, stream); });
         if (e != hipSuccess) return hip_fail(e, "relay launch");
@@ -476,7 +485,7 @@ rr_status relay_launch(const rr_config &c, const RelayBuffers &b, int32_t layer,
         e = launch(RR_KERNEL_REROUTE, [&] { return rr::launch_route(a, c.dtype, grid, stream); });
         if (e != hipSuccess) return hip_fail(e, "reroute launch");
     }
-    if (routes) {
+    if (routes && !b.resident) {
         hipError_t e = hipMemcpyAsync(routes, b.routes, sizeof(int32_t) * rows_of(c) * c.k, hipMemcpyDeviceToDevice,
                                       stream);
         if (e != hipSuccess) return hip_fail(e, "route copy");
@@ -546,7 +555,8 @@ rr_status rr_ledger_create(const rr_config *cfg, rr_ledger **out)
     const RelayPlan plan = relay_plan(*cfg);
     L->bm_words = plan.bm_words;
     L->fused = plan.fused;
-    if ((L->fused && (st = alloc(&L->done, 1, "relay counter")) != RR_OK) ||
+    L->resident = plan.resident;
+    if ((L->fused && (st = alloc(&L->done, kDoneWords, "relay counter")) != RR_OK) ||
         (plan.seeds && ((st = alloc(&L->seed_bound, rows, "seed bounds")) != RR_OK ||
                         (st = alloc(&L->seed_rmax, rows, "seed maxima")) != RR_OK))) {
         free_all(L);
@@ -559,7 +569,7 @@ rr_status rr_ledger_create(const rr_config *cfg, rr_ledger **out)
     if (e == hipSuccess && sent_width(*cfg) > 0) e = hipMemset(L->sent, 0xFF, sizeof(int32_t) * rows * sent_width(*cfg));
     if (e == hipSuccess) e = hipMemset(L->build, 0xFF, sizeof(int32_t) * rows);
     if (e == hipSuccess) e = hipMemset(L->age, 0, sizeof(int32_t) * rows);
-    if (e == hipSuccess && L->done) e = hipMemset(L->done, 0, sizeof(uint32_t));
+    if (e == hipSuccess && L->done) e = hipMemset(L->done, 0, kDoneWords * sizeof(uint32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         free_all(L);
@@ -638,6 +648,7 @@ rr_status rr_relay_layer(rr_ledger *L, int32_t layer, const void *Qc, const void
     b.stat_nrr = L->stat_nrr;
     b.done = L->done;
     b.fused = L->fused;
+    b.resident = L->resident;
     b.bm_words = L->bm_words;
     b.unconverged = ds->unconverged;
     st = relay_launch(L->cfg, b, layer, Qc, Kc, routes, mask, pairs, n_rerouted,
@@ -683,6 +694,7 @@ rr_status rr_relay_layer_static(const rr_config *cfg, int32_t layer, const void 
     b.seed_bound = plan.seeds ? reinterpret_cast<float *>(base + lay.seed_bound) : nullptr;
     b.seed_rmax = plan.seeds ? reinterpret_cast<float *>(base + lay.seed_rmax) : nullptr;
     b.fused = plan.fused;
+    b.resident = plan.resident;
     b.bm_words = plan.bm_words;
     b.unconverged = ds->unconverged;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
@@ -691,7 +703,7 @@ rr_status rr_relay_layer_static(const rr_config *cfg, int32_t layer, const void 
         // area keeps the previous call's contents, so it is cleared here, on
         // the caller's stream, by a kernel (a stream under capture records a
         // plain kernel node, not a memset)
-        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, stream, b.done, 1);
+        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, stream, b.done, kDoneWords);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "relay scratch clear");
     }

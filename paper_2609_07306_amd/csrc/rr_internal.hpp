@@ -59,10 +59,13 @@ struct RouteArgs {
     float *beta_out;           // relay: [rows] max over C
     float gamma;               // relay: guard margin
     int32_t bm_words;          // relay: ledger bitmap row stride in (R, C) word pairs
-    uint32_t *done;            // relay: finished-workgroup counter (0 between launches)
+    uint32_t *done;            // relay: finished-workgroup counter (0 between launches); resident
+                               // tiles: two 64-bit sums, (tiles << 32 | flagged rows) and score pairs
     int64_t *pairs_out;        // optional device scalar
     int64_t pairs_value;       // value written to pairs_out (full / anchor; reroute: the workgroup sums)
     unsigned long long *unconverged;  // device counter: rows whose collection stopped at the sweep cap
+    bool vec;                         // resident tiles: the outputs' rows may be moved in 16-byte pieces (set by the launcher)
+    uint64_t barrett;                 // resident tiles: floor((2^64 - 1) / n_k) (set by the launcher)
     int32_t sweep_cap;                // collection sweeps allowed per tile (kMaxFixIters unless a test lowers it)
 };
 
@@ -113,9 +116,14 @@ hipError_t launch_expand(const int32_t *routes, int64_t rows, int k, int chunk, 
 
 // Supported (dtype, d) combinations; dtype 0 = binary32, 1 = bf16.
 bool route_supported(int dtype, int d, int T);
+// Tile shape of the resident-score kernel (rr_resident_impl.hpp) for a
+// configuration, as 10 * waves + stages, or 0 where it does not apply.
+int resident_shape(int n_k, int T);
 int route_tile_rows(int T, int n_heads, int n_q);  // query rows per route tile for T = k + m
 // Largest ledger bitmap (word pairs per row) a relay tile holds in LDS.
 int route_relay_max_bm_words(int dtype, int d, int T);
 hipError_t launch_route(const RouteArgs &a, int dtype, int grid, hipStream_t stream);
+// Full, anchor and relay launches of the resident-score kernel.
+hipError_t launch_resident(const RouteArgs &a, int dtype, hipStream_t stream);
 
 }  // namespace rr

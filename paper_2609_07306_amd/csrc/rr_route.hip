@@ -33,6 +33,17 @@ int route_tile_rows(int T, int n_heads, int n_q)
     return narrow < kFewTiles ? kSmallTileRows : kNarrowTileRows;
 }
 
+// The resident-score kernel holds a 32-row tile's scores over the whole key
+// range in registers: up to 1024 keys on four waves, 2048 on eight.  Eight
+// lanes per row (four waves) sort 64 scores, sixteen sort 128.
+int resident_shape(int n_k, int T)
+{
+    if (n_k > 2048 || T > 128) return 0;
+    const int nw = (T > 64 || n_k > 1024) ? 8 : 4;
+    const int kt = n_k <= 64 * nw ? 2 : (n_k <= 128 * nw ? 4 : 8);
+    return 10 * nw + kt;
+}
+
 int route_relay_max_bm_words(int dtype, int d, int T)
 {
     using route_detail::relay_max_bm_words;
@@ -45,8 +56,52 @@ int route_relay_max_bm_words(int dtype, int d, int T)
     }
 }
 
+// One instance set per caller, input type and width (rr_resident_inst.hip).
+#define RR_RESIDENT(mode) \
+    hipError_t launch_resident_##mode##_float_32(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_float_64(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_float_128(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_bf16_t_32(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_bf16_t_64(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_bf16_t_128(const RouteArgs &, hipStream_t); \
+    hipError_t launch_resident_##mode##_bf16_t_256(const RouteArgs &, hipStream_t); \
+    static hipError_t launch_resident_##mode(const RouteArgs &a, int dtype, hipStream_t s) \
+    { \
+        if (dtype == 0) { \
+            switch (a.d) { \
+            case 32: return launch_resident_##mode##_float_32(a, s); \
+            case 64: return launch_resident_##mode##_float_64(a, s); \
+            case 128: return launch_resident_##mode##_float_128(a, s); \
+            default: return hipErrorInvalidValue; \
+            } \
+        } \
+        switch (a.d) { \
+        case 32: return launch_resident_##mode##_bf16_t_32(a, s); \
+        case 64: return launch_resident_##mode##_bf16_t_64(a, s); \
+        case 128: return launch_resident_##mode##_bf16_t_128(a, s); \
+        case 256: return launch_resident_##mode##_bf16_t_256(a, s); \
+        default: return hipErrorInvalidValue; \
+        } \
+    }
+RR_RESIDENT(MODE_FULL)
+RR_RESIDENT(MODE_ANCHOR)
+RR_RESIDENT(MODE_RELAY)
+#undef RR_RESIDENT
+
+hipError_t launch_resident(const RouteArgs &a, int dtype, hipStream_t stream)
+{
+    switch (a.mode) {
+    case MODE_FULL: return launch_resident_MODE_FULL(a, dtype, stream);
+    case MODE_ANCHOR: return launch_resident_MODE_ANCHOR(a, dtype, stream);
+    case MODE_RELAY: return launch_resident_MODE_RELAY(a, dtype, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_route(const RouteArgs &a, int dtype, int grid, hipStream_t stream)
 {
+    if (a.mode != MODE_REROUTE && resident_shape(a.n_k, a.k + a.m) != 0)
+        return launch_resident(a, dtype, stream);
     switch (a.mode) {
     case MODE_FULL: return dtype == 0 ? launch_route_f32_full(a, grid, stream) : launch_route_bf16_full(a, grid, stream);
     case MODE_ANCHOR:
