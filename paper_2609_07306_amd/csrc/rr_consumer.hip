@@ -19,6 +19,7 @@
 // operand is read from the row-major V tile with the LDS transpose read.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cmath>
 
 #include "rr_device.hpp"
@@ -90,18 +91,57 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(const T *__restrict_
 
 // ------------------------------------------------------------ expansion
 
-__global__ void expand_kernel(const int32_t *__restrict__ routes, int64_t rows, int k, int chunk, int n_tok,
-                              int32_t *__restrict__ tokens)
+constexpr int kExpandThreads = 256;
+
+// Bound by the writes (4 bytes a token id; the routes are read once per slot
+// and stay in cache).  A workgroup fills a contiguous span of the output,
+// PER pieces of 16 bytes per thread: one 64-bit division finds the span's
+// first slot, the others follow from a 32-bit reciprocal, and a piece that
+// lies inside one slot costs one route load.  VEC = false: the output is not
+// 16-byte aligned and is written element by element.  (A 64-bit division and
+// a 4-byte store per token id took 71 us for 134 MB.)
+template <int PER, bool VEC>
+__global__ __launch_bounds__(kExpandThreads) void expand_kernel(const int32_t *__restrict__ routes, int64_t total,
+                                                               uint32_t chunk, uint32_t recip, int n_tok, int nc,
+                                                               int32_t *__restrict__ tokens)
 {
-    const int nc = (n_tok + chunk - 1) / chunk;
-    const int64_t per_row = (int64_t)k * chunk, total = rows * per_row;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = x / per_row;
-        const int c = (int)(x - r * per_row), s = c / chunk, t = c - s * chunk;
-        const int j = routes[r * k + s];
-        const int64_t u = (int64_t)j * chunk + t;
-        tokens[x] = (j >= 0 && j < nc && u < n_tok) ? (int32_t)u : -1;
+    constexpr int SPAN = 4 * PER * kExpandThreads;
+    const int64_t base = (int64_t)blockIdx.x * SPAN;
+    const int64_t slot0 = base / chunk;
+    const uint32_t t0 = (uint32_t)(base - slot0 * chunk);
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const uint32_t i = 4u * (p * kExpandThreads + threadIdx.x);
+        const int64_t x = base + i;
+        if (x >= total) break;
+        // n / chunk: the reciprocal floor(2^32 / chunk) undershoots by at most
+        // 1 (n < 2^32; chunk = 1 has no 32-bit reciprocal)
+        const uint64_t n = (uint64_t)t0 + i;
+        uint32_t q = chunk == 1 ? (uint32_t)n : (uint32_t)((n * recip) >> 32), r = (uint32_t)(n - (uint64_t)q * chunk);
+        if (r >= chunk) {
+            ++q;
+            r -= chunk;
+        }
+        int64_t s = slot0 + q;
+        int32_t v[4];
+        int j = routes[s];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t u = (uint32_t)j * chunk + r;  // (j < nc: below n_tok + chunk < 2^32)
+            v[e] = ((uint32_t)j < (uint32_t)nc) & (u < (uint32_t)n_tok) ? (int32_t)u : -1;
+            if (++r == chunk && e < 3 && x + e + 1 < total) {
+                r = 0;
+                j = routes[++s];
+            }
+        }
+        if (VEC && x + 3 < total) {
+            u32x4_t o = {(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+            *reinterpret_cast<u32x4_t *>(tokens + x) = o;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x + e < total) tokens[x + e] = v[e];
+        }
     }
 }
 
@@ -466,9 +506,23 @@ hipError_t launch_expand(const int32_t *routes, int64_t rows, int k, int chunk, 
                          hipStream_t stream)
 {
     const int64_t total = rows * k * (int64_t)chunk;
-    const int64_t want = (total + 255) / 256;
-    const unsigned grid = (unsigned)(want < 65536 ? (want > 0 ? want : 1) : 65536);
-    hipLaunchKernelGGL(expand_kernel, dim3(grid), dim3(256), 0, stream, routes, rows, k, chunk, n_tok, tokens);
+    const int nc = (int)(((int64_t)n_tok + chunk - 1) / chunk);
+    const uint32_t recip = chunk == 1 ? 0u : (uint32_t)((1ull << 32) / (uint32_t)chunk);
+    const bool vec = (reinterpret_cast<uintptr_t>(tokens) & 15) == 0;
+    // eight pieces a thread where that still gives every compute unit four
+    // workgroups, else one
+    const int64_t wide = 32 * (int64_t)kExpandThreads, narrow = 4 * (int64_t)kExpandThreads;
+    const bool many = total >= 1024 * wide;
+    const int64_t span = many ? wide : narrow, blocks = (total + span - 1) / span;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), th(kExpandThreads);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, th, 0, stream, routes, total, (uint32_t)chunk, recip, n_tok, nc, tokens);
+    };
+    if (many)
+        vec ? go(expand_kernel<8, true>) : go(expand_kernel<8, false>);
+    else
+        vec ? go(expand_kernel<1, true>) : go(expand_kernel<1, false>);
     return hipGetLastError();
 }
 
