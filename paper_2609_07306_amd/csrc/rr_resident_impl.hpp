@@ -383,10 +383,12 @@ void resident_kernel(RouteArgs a)
             *reinterpret_cast<u32x4_t *>(wst + pos * S::LS + lcol * 16) = breg[u];
         }
     };
-    gload(breg[0], 0, 0);
-    if (S::SUB > 1 || nb > 1) gload(breg[1], S::SUB > 1 ? 0 : 1, S::SUB > 1 ? 1 : 0);
+    // (the query fragment first: loads complete in order, so the wait for the
+    // first stage covers it and no later product waits for younger loads)
     Frag<DT, D> fq;
     fq.load(reinterpret_cast<const DT *>(a.Q) + (g0 + min(l32, nrows - 1)) * D, hh);
+    gload(breg[0], 0, 0);
+    if (S::SUB > 1 || nb > 1) gload(breg[1], S::SUB > 1 ? 0 : 1, S::SUB > 1 ? 1 : 0);
 
     // relay: the wave's rows' ledger ids -> bitmaps.  The first 16 bytes per
     // lane of R and of C are requested here and marked under the sweep.
