@@ -1,5 +1,5 @@
 // Row-wise GEMM + TopK with the score tile resident in registers, for gfx950
-// and key heads of up to 2048 chunks (RouteRelay, arXiv 2609.07306).
+// and key heads of up to 4096 chunks (RouteRelay, arXiv 2609.07306).
 //
 // Callers: MODE_FULL (Eq. (1)-(2)), MODE_ANCHOR (full routing plus the ledger
 // build of Sec. 3.1) and MODE_RELAY (the whole relay layer of Sec. 3.2 in one
@@ -17,6 +17,18 @@
 // sweep's barriers and stores than on its products.)  A wave's keys are its
 // own: they go global -> registers a stage ahead and registers -> the wave's
 // own LDS rows, with no workgroup barrier in the sweep.
+//
+// More than 2048 keys are swept in panels (P = 3, of up to 1536 keys on eight
+// waves of six stages): after each panel the row's bound is raised over the
+// panel's group maxima and the candidates so far, and the list is rewritten from
+// both, so what follows sees one list.  A relay's trigger is known after the last
+// panel only; before it every row keeps a list.  The LDS holds key rows and lists
+// side by side then, with the staging in the key rows' place after the last
+// sweep.  Six stages and one stage in flight instead of eight and two, because a
+// register spilled in the sweep is reloaded behind the keys in flight and waits
+// for them (two panels of eight stages: 7100 cycles a stage, three of six: 3400).
+// Long-context schedule (32 heads x 4096, causal, bf16, T = 96): 2653 us with the
+// two-sweep tiles, 2018 us.
 //
 // Selecting the T = k + m best of a row:
 //   1. bound: per lane and register slot the maximum over the stages, so a
@@ -63,7 +75,7 @@ using route_detail::transposed_row;
 constexpr int kBoundRounds = 3;  // times the bound's range is cut into levels, at most
 constexpr float kLowest = -FLT_MAX;  // threshold that admits every valid score (masked keys hold -inf)
 
-template <typename DT, int D, int NW, int KT>
+template <typename DT, int D, int NW, int KT, int P>
 struct Shape {
     static constexpr int NT = 64 * NW, BM = 32, NSEG = 2 * NW;
     static constexpr int ROWB = D * (int)sizeof(DT);
@@ -78,14 +90,18 @@ struct Shape {
     static constexpr int WST = (32 * LS > 32 * KSTR * 4) ? 32 * LS : 32 * KSTR * 4;  // a wave's LDS rows
     static constexpr int LPR = NSEG;          // lanes per row after the sweep
     static constexpr int RPW = 64 / LPR;      // rows per wave
-    static constexpr int CPL = 16, CAP = CPL * LPR;  // candidates per lane and row
+    static constexpr int CPL = P > 1 ? 12 : 16, CAP = CPL * LPR;  // candidates per lane and row
     static constexpr int LSTR = CAP * 8 + 64;        // row stride of the candidate lists (bytes)
     static constexpr int NET = 8 * LPR;              // scores the sorting network holds
-    static constexpr int NWD = KT * NW;              // words of a bitmap over the padded keys
+    static constexpr int NWD = P > 1 ? 128 : KT * NW;  // words of a bitmap over the padded keys
     static constexpr int BW = NWD + 1;               // its row stride in word pairs
     static constexpr int WPL = NWD / LPR;            // words per lane
+    // LDS of one panel: key rows or candidate lists, bitmaps, prefix counts, staging
     static constexpr int R0 = (NW * WST > BM * LSTR) ? NW * WST : BM * LSTR;
     static constexpr int OFF_BM = R0, OFF_PRE = OFF_BM + BM * BW * 8, OFF_STG = OFF_PRE + BM * NWD * 4;
+    // ... of several: the lists outlive a panel, so the prefix counts and the
+    // staging (needed after the last sweep) share the key rows' region instead
+    __host__ __device__ static constexpr int region(int staged) { return NW * WST > BM * NWD * 4 + staged ? NW * WST : BM * NWD * 4 + staged; }
     static_assert(NWD % LPR == 0 && WPL >= 1 && PT >= 1 && OFF_STG % 16 == 0, "layout");
 };
 
@@ -292,21 +308,45 @@ __device__ __forceinline__ void append16(const f32x16_t &s, float th, uint32_t &
 #undef RR_CMP
 }
 
+// The same for N (a multiple of four) scores with an id each.
+template <int N>
+__device__ __forceinline__ void append_listed(const float (&x)[N], const uint32_t (&id)[N], float th, uint32_t &at)
+{
+    static_assert(N % 4 == 0, "groups of four");
+#define RR_CMP(m) "v_cmp_ge_f32_e64 %[m" #m "], %[x" #m "], %[th]\n\t"
+#define RR_APP(m) \
+    "s_mov_b64 exec, %[m" #m "]\n\t" \
+    "ds_write2_b32 %[at], %[x" #m "], %[i" #m "] offset0:0 offset1:1\n\t" \
+    "v_add_u32_e32 %[at], 8, %[at]\n\t"
+#pragma unroll
+    for (int b = 0; b < N; b += 4) {
+        uint64_t sv, m0, m1, m2, m3;
+        asm volatile("s_mov_b64 %[sv], exec\n\t" RR_CMP(0) RR_CMP(1) RR_CMP(2) RR_CMP(3) RR_APP(0) RR_APP(1) RR_APP(2)
+                         RR_APP(3) "s_mov_b64 exec, %[sv]\n\t"
+                     : [at] "+v"(at), [sv] "=&s"(sv), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3)
+                     : [x0] "v"(x[b]), [x1] "v"(x[b + 1]), [x2] "v"(x[b + 2]), [x3] "v"(x[b + 3]), [i0] "v"(id[b]),
+                       [i1] "v"(id[b + 1]), [i2] "v"(id[b + 2]), [i3] "v"(id[b + 3]), [th] "v"(th)
+                     : "memory");
+    }
+#undef RR_APP
+#undef RR_CMP
+}
+
 // Waves per SIMD the registers should allow: the accumulators take 16 KT, the
 // query fragment and a stage in flight ROWB / 8 and RB / 8 each.
 template <typename DT, int D, int NW, int KT>
 constexpr int min_waves()
 {
-    using S = Shape<DT, D, NW, KT>;
+    using S = Shape<DT, D, NW, KT, 1>;
     const int regs = 16 * KT + S::ROWB / 8 + S::RB / 4 + 40;
     return regs <= 168 ? 3 : (regs <= 264 ? 2 : 1);
 }
 
-template <int MODE, typename DT, int D, int NW, int KT>
+template <int MODE, typename DT, int D, int NW, int KT, int P>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, 64 * NW), amdgpu_waves_per_eu(min_waves<DT, D, NW, KT>())))
 void resident_kernel(RouteArgs a)
 {
-    using S = Shape<DT, D, NW, KT>;
+    using S = Shape<DT, D, NW, KT, P>;
     constexpr int LPR = S::LPR, RPW = S::RPW, CAP = S::CAP;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float th_s[32], rmax_s[32];
@@ -315,15 +355,19 @@ void resident_kernel(RouteArgs a)
     __shared__ unsigned long long s_pairs;
     __shared__ int32_t s_rows;
 
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = lane >> 5, l32 = lane & 31;
+    int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int hh = lane >> 5, l32 = lane & 31;
     const int group = a.n_heads / a.n_kv_heads;
     const int n_mand = a.n_sink + a.n_recent, c_sent = a.m + a.r + n_mand;
     // LDS strides of the staged rows (int32), multiples of four
     const int k4 = (a.k + 3) & ~3, c4 = (c_sent + 3) & ~3, r4 = (a.r + 3) & ~3;
-    uint2 *bm = reinterpret_cast<uint2 *>(smem + S::OFF_BM);        // [32][BW] (R, N or ledger R, C) words
-    uint32_t *pre = reinterpret_cast<uint32_t *>(smem + S::OFF_PRE);  // [32][NWD] counts before a word: R | N << 16
-    int32_t *stgR = reinterpret_cast<int32_t *>(smem + S::OFF_STG);  // [32][k4]
+    unsigned char *const lists = smem + (P > 1 ? a.lds_region0 : 0);  // [32][LSTR] candidates
+    // [32][BW] (R, N or ledger R, C) words
+    uint2 *bm = reinterpret_cast<uint2 *>(P > 1 ? lists + S::BM * S::LSTR : smem + S::OFF_BM);
+    // [32][NWD] counts before a word: R | N << 16
+    uint32_t *pre = reinterpret_cast<uint32_t *>(smem + (P > 1 ? 0 : S::OFF_PRE));
+    int32_t *stgR = reinterpret_cast<int32_t *>(smem + (P > 1 ? S::BM * S::NWD * 4 : S::OFF_STG));  // [32][k4]
     int32_t *stgS = stgR + 32 * k4;                                  // [32][c4]; full routing: slot scores [32][k4]
     int32_t *dra = stgS + 32 * c4;                                   // [32][r4] random draws
 
@@ -337,36 +381,49 @@ void resident_kernel(RouteArgs a)
     const int nrows = min(32, a.n_q - i0);
     const int64_t g0 = (int64_t)h * a.n_q + i0;
     const int ncols = a.causal ? min(i0 + nrows, a.n_k) : a.n_k;
-    const int nb = (ncols + 32 * NW - 1) / (32 * NW);  // stages, <= KT
-    const int seg = 16 * nb;
+    const int nbt = (ncols + 32 * NW - 1) / (32 * NW);  // stages, <= P KT
+    const int np = P > 1 ? (nbt + KT - 1) / KT : 1;     // panels
+    int nb = P > 1 ? (nbt + np - 1) / np : nbt;         // stages of the panel, <= KT
+    int seg = 16 * nb, kp = 0;                          // its segments' length and its first key
     const unsigned char *Kg = reinterpret_cast<const unsigned char *>(a.K) + (int64_t)(h / group) * a.n_k * S::ROWB;
 
     // ---- after the sweep, lane (rl, part) of wave w serves row sr
-    const int part = lane & (LPR - 1), sr = w * RPW + lane / LPR;
-    const int64_t grow = g0 + min(sr, nrows - 1);  // (rows past the tile's last repeat it and write nothing)
+    int part = lane & (LPR - 1), sr = w * RPW + lane / LPR;
+    int64_t grow = g0 + min(sr, nrows - 1);  // (rows past the tile's last repeat it and write nothing)
 
     // ------------------------------------------------------ requests, set-up
     // global -> registers: this lane's pieces of part q of stage st (keys past
     // the last repeat it; their scores are masked)
-    u32x4_t breg[2][S::PT];  // two stage parts in flight
+    constexpr int NF = P > 1 ? 1 : 2;  // stage parts in flight (one: the panel loop needs the registers)
+    u32x4_t breg[NF][S::PT];
     const bool whole = (2 * w + 2) * seg <= a.n_k;  // every key of the wave's segments exists
-    const uint32_t lrow = lane / S::PR, lcol = lane % S::PR;
+    uint32_t lrow = lane / S::PR, lcol = lane % S::PR;
+    const __amdgpu_buffer_rsrc_t keys =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(Kg), 0, a.n_k * S::ROWB, 0x00020000);
     auto gload = [&](u32x4_t (&breg)[S::PT], int st, int q) __attribute__((always_inline)) {
         const uint32_t coff = (lcol / (S::PR / 2)) * (S::ROWB / 2) + q * (S::RB / 2) + (lcol % (S::PR / 2)) * 16;
         constexpr int RS = 64 / S::PR;  // key rows a wave loads at a time
-        if (whole) {
+        if constexpr (P > 1) {
+            // (bounded by the key head: keys past the last read as zero)
+#pragma unroll
+            for (int u = 0; u < S::PT; ++u) {
+                const int tr = u * RS;
+                const uint32_t key = kp + (2 * w + tr / 16) * seg + 16 * st + tr % 16;
+                breg[u] = __builtin_amdgcn_raw_buffer_load_b128(keys, lrow * S::ROWB + coff + key * S::ROWB, 0, 0);
+            }
+        } else if (whole) {
             const uint32_t voff = lrow * S::ROWB + coff;
 #pragma unroll
             for (int u = 0; u < S::PT; ++u) {
                 const int tr = u * RS;  // (RS divides 16)
-                const unsigned char *base = Kg + (int64_t)((2 * w + tr / 16) * seg + 16 * st + tr % 16) * S::ROWB;
+                const unsigned char *base = Kg + (int64_t)(kp + (2 * w + tr / 16) * seg + 16 * st + tr % 16) * S::ROWB;
                 breg[u] = *reinterpret_cast<const u32x4_t *>(base + voff);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < S::PT; ++u) {
                 const int tr = u * RS + (int)lrow;
-                const int key = min((2 * w + (tr >> 4)) * seg + 16 * st + (tr & 15), a.n_k - 1);
+                const int key = min(kp + (2 * w + (tr >> 4)) * seg + 16 * st + (tr & 15), a.n_k - 1);
                 breg[u] = *reinterpret_cast<const u32x4_t *>(Kg + (uint32_t)key * S::ROWB + coff);
             }
         }
@@ -386,9 +443,15 @@ void resident_kernel(RouteArgs a)
     // (the query fragment first: loads complete in order, so the wait for the
     // first stage covers it and no later product waits for younger loads)
     Frag<DT, D> fq;
-    fq.load(reinterpret_cast<const DT *>(a.Q) + (g0 + min(l32, nrows - 1)) * D, hh);
-    gload(breg[0], 0, 0);
-    if (S::SUB > 1 || nb > 1) gload(breg[1], S::SUB > 1 ? 0 : 1, S::SUB > 1 ? 1 : 0);
+    const DT *const Qrow = reinterpret_cast<const DT *>(a.Q) + (g0 + min(l32, nrows - 1)) * D;
+    fq.load(Qrow, hh);
+    auto gload_first = [&]() __attribute__((always_inline)) {
+        gload(breg[0], 0, 0);
+        if constexpr (NF > 1) {
+            if (S::SUB > 1 || nb > 1) gload(breg[NF - 1], S::SUB > 1 ? 0 : 1, S::SUB > 1 ? 1 : 0);
+        }
+    };
+    gload_first();
 
     // relay: the wave's rows' ledger ids -> bitmaps.  The first 16 bytes per
     // lane of R and of C are requested here and marked under the sweep.
@@ -439,20 +502,25 @@ void resident_kernel(RouteArgs a)
 
     // ------------------------------------------------------------- the sweep
     const int myn = l32 < nrows ? (a.causal ? min(i0 + l32 + 1, a.n_k) : a.n_k) : 0;  // valid keys of the lane's row
-    const int kbase = (2 * w + hh) * seg;                                             // first key of its segment
+    int kbase = (2 * w + hh) * seg;                                                   // first key of its segment
     const int minn = a.causal ? i0 + 1 : a.n_k;                                       // least over the tile's rows
     f32x16_t acc[KT];
     float amin = INFINITY, bmax = -INFINITY;
+    // (several panels: a stage's limits are formed where they are used, not kept for
+    // every stage of the panel loop)
     auto finish = [&](f32x16_t &x, int st) __attribute__((always_inline)) {
-        if ((2 * w + 1) * seg + 16 * st + 16 > minn) {  // (wave-uniform) some key is invalid for some row
-            const int vlim = myn - (kbase + 16 * st);
+        if (kp + (2 * w + 1) * seg + 16 * st + 16 > minn) {  // (wave-uniform) some key is invalid for some row
+            int my = myn;
+            if (P > 1) asm volatile("" : "+v"(my));
+            const int vlim = my - (kbase + 16 * st);
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] = (i < vlim) ? x[i] : -INFINITY;
         }
         if constexpr (MODE == MODE_RELAY) {
             // alpha = min over R, beta = max over C, by bit-select from the
             // ledger's bitmaps
-            const int k0 = kbase + 16 * st;
+            int k0 = kbase + 16 * st;
+            if (P > 1) asm volatile("" : "+v"(k0));
             const uint2 wv = bm[l32 * S::BW + (k0 >> 5)];
             const uint32_t sh = (uint32_t)(k0 & 16);
             const uint32_t mr = wv.x >> sh, mc = wv.y >> sh;
@@ -466,18 +534,44 @@ void resident_kernel(RouteArgs a)
             }
         }
     };
-    const unsigned char *lp = wst + l32 * S::LS + hh * (S::RB / 2);
+    bool on = sr < nrows, routed = false;  // row sr, row l32: routed by this launch
+    unsigned long long pub = 0;  // relay: what the launch's pair total was before this tile's
+    unsigned long long fin = 0;  // relay: tiles finished before this one << 32 | their flagged rows
+    if constexpr (P > 1 && MODE == MODE_RELAY) mark_ledger();
+    for (int p = 0;; ++p) {
+    const bool last = P == 1 || p == np - 1;
+    if constexpr (P > 1) {
+        // (opaque: values derived from the lane are formed again in each panel
+        // instead of being kept in registers across the sweeps)
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        hh = lane >> 5;
+        l32 = lane & 31;
+        lrow = lane / S::PR;
+        lcol = lane % S::PR;
+    }
+    if (P > 1 && p > 0) {
+        kp += 32 * NW * nb;
+        nb = min(nb, nbt - p * nb);
+        seg = 16 * nb;
+        kbase = kp + (2 * w + hh) * seg;
+        if (tid < 96) row_cnt[tid >> 5][tid & 31] = 0;
+        fq.load(Qrow, hh);  // (loaded again: kept, it would cost the collection its registers)
+        gload_first();
+    }
+    const unsigned char *const lp = wst + l32 * S::LS + hh * (S::RB / 2);
     // relay: the ledger's marks (and their barrier) come under stage `mst`
-    const int mst = min(KT > 2 ? 2 : 0, nb - 1);
+    // (several panels: before the first)
+    const int mst = P > 1 ? -1 : min(KT > 2 ? 2 : 0, nb - 1);
     static_for<KT>([&](auto sc) __attribute__((always_inline)) {
         constexpr int st = decltype(sc)::value;
         if (st < nb) {
             f32x16_t c = f32x16_t{};
             static_for<S::SUB>([&](auto qc) __attribute__((always_inline)) {
                 constexpr int q = decltype(qc)::value, x = st * S::SUB + q;  // x: the part's number
-                constexpr int nst = (x + 2) / S::SUB, nq = (x + 2) % S::SUB;
-                lstore(breg[x & 1]);
-                if (nst < nb) gload(breg[x & 1], nst, nq);
+                constexpr int nst = (x + NF) / S::SUB, nq = (x + NF) % S::SUB;
+                lstore(breg[x % NF]);
+                if (nst < nb) gload(breg[x % NF], nst, nq);
                 wave_sync();
                 c = KeyPart<DT, D, S::SUB>::mma(lp, fq, q, c);
                 if (q == S::SUB - 1) {
@@ -488,7 +582,7 @@ void resident_kernel(RouteArgs a)
                 }
                 wave_sync();
             });
-            if constexpr (MODE == MODE_RELAY && st <= (KT > 2 ? 2 : 0)) {
+            if constexpr (P == 1 && MODE == MODE_RELAY && st <= (KT > 2 ? 2 : 0)) {
                 if (st == mst) {
                     mark_ledger();
                     static_for<st>([&](auto jc) __attribute__((always_inline)) { finish(acc[decltype(jc)::value], decltype(jc)::value); });
@@ -517,7 +611,7 @@ void resident_kernel(RouteArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             reinterpret_cast<float4 *>(kp)[q] = make_float4(gm[4 * q], gm[4 * q + 1], gm[4 * q + 2], gm[4 * q + 3]);
-        if constexpr (MODE == MODE_RELAY) {
+        if (MODE == MODE_RELAY && last) {
             amin = fminf(amin, __shfl_xor(amin, 32, 64));
             bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
             if (hh == 0) ab_s[w][l32] = make_float2(amin, bmax);
@@ -526,8 +620,14 @@ void resident_kernel(RouteArgs a)
     lds_barrier();
 
     // ------------------------------------------------- trigger, bound per row
-    bool on = sr < nrows;  // the row is routed by this launch
-    if constexpr (MODE == MODE_RELAY) {
+    if constexpr (P > 1) {
+        asm volatile("" : "+v"(tid));
+        part = tid & (LPR - 1);
+        sr = w * RPW + (tid & 63) / LPR;
+        grow = g0 + min(sr, nrows - 1);
+    }
+    // (before the last panel every row counts as routed)
+    if (MODE == MODE_RELAY && last) {
         const float2 x = ab_s[part & (NW - 1)][sr];
         const float al = row_min<LPR>(x.x), be = row_max<LPR>(x.y);
         int flagged = 0;
@@ -548,7 +648,19 @@ void resident_kernel(RouteArgs a)
     }
     {
         const float4 *kp = reinterpret_cast<const float4 *>(smem + (part >> 1) * S::WST) + sr * (S::KSTR / 4) + (part & 1) * 4;
-        float u[16];
+        // a later panel takes the candidates so far as well
+        constexpr int NU = P > 1 ? 16 + S::CPL : 16;
+        const int c1 = (P > 1 && p > 0) ? row_c[sr] : 0;
+        const bool dead = P > 1 && p > 0 && c1 == 0;  // stopped at the sweep cap: keeps no candidate
+        float u[NU];
+        if constexpr (P > 1) {
+            const uint2 *lst = reinterpret_cast<const uint2 *>(lists + sr * S::LSTR);
+#pragma unroll
+            for (int j = 0; j < S::CPL; ++j) {
+                u[16 + j] = -INFINITY;
+                if (part + LPR * j < c1) u[16 + j] = __uint_as_float(lst[part + LPR * j].x);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float4 x = kp[q];
@@ -560,7 +672,7 @@ void resident_kernel(RouteArgs a)
         float rmax = u[0], umin = INFINITY;
         int nfin = 0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < NU; ++q) {
             const bool fin = u[q] > -INFINITY;
             rmax = fmaxf(rmax, u[q]);
             umin = fminf(umin, fin ? u[q] : INFINITY);
@@ -578,14 +690,15 @@ void resident_kernel(RouteArgs a)
         // 0.51 steps below.  Where much of the row falls into one level (an
         // outlier stretches the range) that level is cut again.
         float lo = nfin >= T ? umin : kLowest, hi = rmax;
+        if (P > 1 && p > 0) lo = fmaxf(lo, th_s[sr]);
         int clo = nfin;
         for (int it = 0; it < kBoundRounds; ++it) {
             const bool go = on & (nfin >= T) & (clo > T + (T >> 3)) & (hi > lo);
             if (__ballot(go) == 0ull) break;
             const float step = (hi - lo) * (1.0f / 127.0f), inv = 127.0f * __builtin_amdgcn_rcpf(hi - lo);
-            uint32_t x[4];
+            uint32_t x[NU / 4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < NU / 4; ++q) {
                 uint32_t b = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -599,7 +712,7 @@ void resident_kernel(RouteArgs a)
                 const uint32_t p = lev | b;
                 int n = 0;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) n += __popc((x[q] - p) & 0x80808080u);
+                for (int q = 0; q < NU / 4; ++q) n += __popc((x[q] - p) & 0x80808080u);
                 n = row_sum<LPR>(n);
                 lev = n >= T ? p : lev;
                 cl = n >= T ? n : cl;
@@ -612,13 +725,12 @@ void resident_kernel(RouteArgs a)
             }
         }
         if (part == 0) {
-            th_s[sr] = on ? lo : INFINITY;
-            rmax_s[sr] = rmax;
+            th_s[sr] = (on & !dead) ? lo : INFINITY;
+            rmax_s[sr] = P > 1 ? (on ? (dead ? INFINITY : rmax) : 0.f) : rmax;
         }
     }
     lds_barrier();
-    unsigned long long pub = 0;  // relay: what the launch's pair total was before this tile's
-    if constexpr (MODE == MODE_RELAY) {
+    if (MODE == MODE_RELAY && last) {
         if (tid == 0)
             pub = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.done) + 1, s_pairs, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
@@ -627,15 +739,41 @@ void resident_kernel(RouteArgs a)
     // ------------------------------------------- collection into row lists
     // (every wave follows all 32 rows: lane (l32, hh) holds row l32's state)
     float th = th_s[l32];
-    const bool routed = th < INFINITY;
+    routed = P > 1 ? (th < INFINITY) | (rmax_s[l32] == INFINITY) : th < INFINITY;
+    const int nv = last ? myn : min(myn, kp + 32 * NW * nb);  // the row's valid keys so far
     int base = 0, cnt = 0;
     {
         int th_id = INT_MAX, state = 0, id_lo = -1, id_hi = 0;  // state 1: cutting ties at th by id
         uint32_t lk = float_order(th), hk = float_order(rmax_s[l32]) + 1u;
         bool settled = true, ties = false;
         int total = 0;
+        // the candidates so far, rewritten with this panel's: every 2 NW-th is this lane's
+        constexpr int NX = P > 1 ? S::CPL : 1;
+        float xs[NX];
+        uint32_t xi[NX];
+        const bool more_lists = P > 1 && p > 0;
+        if constexpr (P > 1) {
+            const int c1 = p > 0 ? row_c[l32] : 0;
+            const uint2 *lst = reinterpret_cast<const uint2 *>(lists + l32 * S::LSTR);
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                const int e = 2 * w + hh + LPR * j;
+                xs[j] = -INFINITY;
+                xi[j] = 0;
+                if (e < c1) {
+                    const uint2 x = lst[e];
+                    xs[j] = __uint_as_float(x.x);
+                    xi[j] = x.y;
+                }
+            }
+        }
         for (int it = 0;; ++it) {
             cnt = 0;
+            if (more_lists) {
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    cnt += (ties ? (xs[j] > th) | ((xs[j] == th) & ((int)xi[j] <= th_id)) : xs[j] >= th) ? 1 : 0;
+            }
             if (!ties) {
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {
@@ -666,13 +804,13 @@ void resident_kernel(RouteArgs a)
             bool again = false;
             // the row's least admissible count (T_i <= T; rows not routed admit nothing)
             if (it == 0) {
-                const bool few = (th < INFINITY) & (total < min(a.k + a.m, myn));
+                const bool few = (th < INFINITY) & (total < min(a.k + a.m, nv));
                 if (__ballot((total > CAP) | few) == 0ull) break;  // the usual case
                 if (few) lk = float_order(kLowest);  // (the bound's rounding overshot: not a lower bound)
             }
             if (th < INFINITY) {
                 const int ki = a.k_rows ? min(max(a.k_rows[g0 + min(l32, nrows - 1)], 1), a.k) : a.k;
-                const int Ti = ki + a.m, need = min(Ti, myn);
+                const int Ti = ki + a.m, need = min(Ti, nv);
                 if (state == 1) {
                     const int mid = th_id;
                     if (total >= need)
@@ -702,8 +840,8 @@ void resident_kernel(RouteArgs a)
                         state = 1;
                         th = order_float(lk);
                         id_lo = -1;
-                        id_hi = myn - 1;
-                        th_id = -1 + (myn >> 1);
+                        id_hi = nv - 1;
+                        th_id = -1 + (nv >> 1);
                     }
                 }
             }
@@ -726,14 +864,26 @@ void resident_kernel(RouteArgs a)
             if (!settled && a.unconverged) atomicAdd(a.unconverged, 1ull);
         }
         if (!ties) {
-            uint32_t at = (uint32_t)(l32 * S::LSTR + base * 8) + lds_offset(smem);
+            uint32_t at = (uint32_t)(l32 * S::LSTR + base * 8) + lds_offset(lists);
+            if constexpr (P > 1) {
+                if (p > 0) append_listed<NX>(xs, xi, th, at);
+            }
             static_for<KT>([&](auto sc) __attribute__((always_inline)) {
                 constexpr int st = decltype(sc)::value;
                 if (st < nb) append16(acc[st], th, at, (uint32_t)(kbase + 16 * st));
             });
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         } else {
-            uint2 *lst = reinterpret_cast<uint2 *>(smem + l32 * S::LSTR) + base;
+            uint2 *lst = reinterpret_cast<uint2 *>(lists + l32 * S::LSTR) + base;
+            if (more_lists) {
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    if ((xs[j] > th) | ((xs[j] == th) & ((int)xi[j] <= th_id))) {
+                        *lst = make_uint2(__float_as_uint(xs[j]), xi[j]);
+                        ++lst;
+                    }
+                }
+            }
 #pragma unroll
             for (int st = 0; st < KT; ++st) {
                 if (st < nb) {
@@ -749,8 +899,7 @@ void resident_kernel(RouteArgs a)
             }
         }
     }
-    unsigned long long fin = 0;  // relay: tiles finished before this one << 32 | their flagged rows
-    if constexpr (MODE == MODE_RELAY) {
+    if (MODE == MODE_RELAY && last) {
         // published after the pair total has been added (pub has returned)
         if (tid == 0) {
             asm volatile("" : "+v"(pub)::"memory");
@@ -759,6 +908,8 @@ void resident_kernel(RouteArgs a)
         }
     }
     lds_barrier();
+    if (last) break;
+    }
 
     // -------------------------------------------- selection (row's own lanes)
     // Slot `slot` of the tile (staging, bitmaps) serves row `row`.  A relay's
@@ -782,16 +933,16 @@ void resident_kernel(RouteArgs a)
         }
     };
     if (MODE == MODE_RELAY && !on && sr < nrows && a.routes_out) {  // a kept route
-        if (vr && a.k <= 4 * LPR) {
+        if (P == 1 && vr && a.k <= 4 * LPR) {
             if (4 * part < a.k) reinterpret_cast<int4 *>(a.routes_out + grow * a.k)[part] = led_r;
         } else {
-            put_row(a.routes_out + grow * a.k, lr_row, a.k);
+            put_row(a.routes_out + grow * a.k, a.led_routes + grow * a.k, a.k);
         }
     }
     if (__ballot(act) != 0ull) {
         const int64_t orow = g0 + min(row, nrows - 1);
         const int ni = act ? (a.causal ? min(i0 + row + 1, a.n_k) : a.n_k) : 0;
-        const uint2 *lst = reinterpret_cast<const uint2 *>(smem + row * S::LSTR);
+        const uint2 *lst = reinterpret_cast<const uint2 *>(lists + row * S::LSTR);
         const int c = act ? row_c[row] : 0;
         const int ki = a.k_rows ? min(max(a.k_rows[orow], 1), a.k) : a.k;
         const int ke = min(ki, c), Te = min(ki + a.m, c);
@@ -1000,7 +1151,9 @@ void resident_kernel(RouteArgs a)
                     // Bit j of `pend`: slot part + LPR j has no proposal; byte j of
                     // `tried`: its attempts so far.  Few slots need a second attempt,
                     // so after the first a lane retries one slot at a time.
-                    uint8_t *const claim = smem + row * S::LSTR;
+                    // (Several panels: the list is shorter than the chunks, and a slot compares
+                    // its proposal with the earlier slots' instead.)
+                    uint8_t *const claim = lists + row * S::LSTR;
                     uint32_t pend = 0;
                     uint64_t tried = 0x0101010101010101ull;
                     bool out = false;  // a slot ran out of attempts
@@ -1013,15 +1166,38 @@ void resident_kernel(RouteArgs a)
                             const int z = probe(s, 0);
                             if (marked(z)) {
                                 pend |= 1u << j;
+                                if (P > 1) dr[s] = -1;
                             } else {
                                 dr[s] = z;
-                                claim[z] = (uint8_t)s;
+                                if (P == 1) claim[z] = (uint8_t)s;
                             }
                         }
                     }
                     for (;;) {
                         wave_sync();
                         bool again = false;
+                        if constexpr (P > 1) {
+                            int z[SPL];
+                            uint32_t hit = 0;
+#pragma unroll
+                            for (int j = 0; j < SPL; ++j) {
+                                const int s = part + LPR * j;
+                                z[j] = (go & (s < a.r) & (((pend >> j) & 1u) == 0u)) ? dr[s] : -2;
+                            }
+                            for (int t = 0; t < min(a.r, SPL * LPR); t += 4) {
+                                const int4 y = *reinterpret_cast<const int4 *>(dr + t);
+#pragma unroll
+                                for (int j = 0; j < SPL; ++j) {
+                                    if (LPR * j < a.r) {  // (uniform)
+                                        const int n = part + LPR * j - t;  // earlier slots among the four
+                                        const bool x = ((y.x == z[j]) & (n > 0)) | ((y.y == z[j]) & (n > 1)) |
+                                                       ((y.z == z[j]) & (n > 2)) | ((y.w == z[j]) & (n > 3));
+                                        hit |= x ? 1u << j : 0u;
+                                    }
+                                }
+                            }
+                            pend |= hit;
+                        } else
                         for (int j = 0; LPR * j < a.r; ++j) {  // (uniform)
                             const int s = part + LPR * j;
                             if (go & (s < a.r) & (((pend >> j) & 1u) == 0u)) {
@@ -1054,7 +1230,7 @@ void resident_kernel(RouteArgs a)
                             }
                             if (z >= 0) {
                                 dr[s] = z;
-                                claim[z] = (uint8_t)s;
+                                if (P == 1) claim[z] = (uint8_t)s;
                                 pend &= pend - 1u;
                             }
                             out = tt >= 64;
@@ -1177,25 +1353,27 @@ void resident_kernel(RouteArgs a)
     }
 }
 
-template <int MODE, typename DT, int D, int NW, int KT>
+template <int MODE, typename DT, int D, int NW, int KT, int P = 1>
 hipError_t launch_t(RouteArgs a, hipStream_t stream)
 {
-    using S = Shape<DT, D, NW, KT>;
+    using S = Shape<DT, D, NW, KT, P>;
     const int c_sent = MODE == MODE_FULL ? 0 : a.m + a.r + a.n_sink + a.n_recent;
     const int k4 = (a.k + 3) & ~3, c4 = (c_sent + 3) & ~3, r4 = (a.r + 3) & ~3;
     const int second = MODE == MODE_FULL ? (a.scores_out ? k4 : 0) : c4 + r4;
-    const size_t lds = (size_t)S::OFF_STG + (size_t)32 * 4 * (k4 + second);
-    if (a.n_k > 32 * NW * KT || a.k + a.m > S::NET) return hipErrorInvalidValue;
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<MODE, DT, D, NW, KT>);
+    const int staged = 32 * 4 * (k4 + second);
+    a.lds_region0 = P > 1 ? S::region(staged) : 0;
+    const size_t lds = P > 1 ? (size_t)a.lds_region0 + S::BM * (S::LSTR + S::BW * 8) : (size_t)S::OFF_STG + staged;
+    if (a.n_k > (P > 1 ? 32 * S::NWD : 32 * NW * KT) || a.k + a.m > S::NET) return hipErrorInvalidValue;
+    const void *fn = reinterpret_cast<const void *>(&resident_kernel<MODE, DT, D, NW, KT, P>);
     static LdsLimit seen;
     hipError_t e = raise_lds_limit(fn, lds, seen);
     if (e != hipSuccess) return e;
     if (a.sweep_cap < 1) a.sweep_cap = kMaxFixIters;
     a.tiles_per_head = (a.n_q + S::BM - 1) / S::BM;
-    a.barrett = max_u64_div_small((uint32_t)a.n_k);  // (n_k <= 2048)
+    a.barrett = max_u64_div_small((uint32_t)a.n_k);  // (n_k <= 4096)
     const auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     a.vec = al(a.led_routes) && al(a.led_sent) && al(a.routes_out) && al(a.scores_out);
-    hipLaunchKernelGGL((resident_kernel<MODE, DT, D, NW, KT>), dim3(a.n_heads * a.tiles_per_head), dim3(64 * NW), lds,
+    hipLaunchKernelGGL((resident_kernel<MODE, DT, D, NW, KT, P>), dim3(a.n_heads * a.tiles_per_head), dim3(64 * NW), lds,
                        stream, a);
     return hipGetLastError();
 }
@@ -1203,13 +1381,14 @@ hipError_t launch_t(RouteArgs a, hipStream_t stream)
 template <int MODE, typename DT, int D>
 hipError_t launch_d(const RouteArgs &a, hipStream_t stream)
 {
-    switch (resident_shape(a.n_k, a.k + a.m)) {
+    switch (resident_shape(a.n_k, a.k, a.m, a.mode == MODE_FULL ? 0 : a.r, a.mode == MODE_FULL ? 0 : a.n_sink + a.n_recent)) {
     case 42: return launch_t<MODE, DT, D, 4, 2>(a, stream);
     case 44: return launch_t<MODE, DT, D, 4, 4>(a, stream);
     case 48: return launch_t<MODE, DT, D, 4, 8>(a, stream);
     case 82: return launch_t<MODE, DT, D, 8, 2>(a, stream);
     case 84: return launch_t<MODE, DT, D, 8, 4>(a, stream);
     case 88: return launch_t<MODE, DT, D, 8, 8>(a, stream);
+    case 386: return launch_t<MODE, DT, D, 8, 6, 3>(a, stream);
     default: return hipErrorInvalidValue;
     }
 }

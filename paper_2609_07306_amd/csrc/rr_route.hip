@@ -33,12 +33,24 @@ int route_tile_rows(int T, int n_heads, int n_q)
     return narrow < kFewTiles ? kSmallTileRows : kNarrowTileRows;
 }
 
+// Slots a tile of several panels may stage per row: its key rows' region takes 416
+// (128 bytes each) beside the prefix counts, and 160 KB of LDS leave room for
+// some more.
+constexpr int kPanelSlots = 440;
+
 // The resident-score kernel holds a 32-row tile's scores over the whole key
-// range in registers: up to 1024 keys on four waves, 2048 on eight.  Eight
+// range in registers: up to 1024 keys on four waves, 2048 on eight, and 4096 in
+// panels on eight (causal 32 x 4096 anchor and two relays: 2653 us by two-sweep
+// tiles, 2018 us).  Eight
 // lanes per row (four waves) sort 64 scores, sixteen sort 128.
-int resident_shape(int n_k, int T)
+int resident_shape(int n_k, int k, int m, int r, int n_mand)
 {
-    if (n_k > 2048 || T > 128) return 0;
+    const int T = k + m;
+    if (n_k > 4096 || T > 128) return 0;
+    if (n_k > 2048) {
+        const auto up = [](int x) { return (x + 3) & ~3; };
+        return up(k) + up(m + r + n_mand) + up(r) <= kPanelSlots ? 386 : 0;
+    }
     const int nw = (T > 64 || n_k > 1024) ? 8 : 4;
     const int kt = n_k <= 64 * nw ? 2 : (n_k <= 128 * nw ? 4 : 8);
     return 10 * nw + kt;
@@ -100,7 +112,8 @@ hipError_t launch_resident(const RouteArgs &a, int dtype, hipStream_t stream)
 
 hipError_t launch_route(const RouteArgs &a, int dtype, int grid, hipStream_t stream)
 {
-    if (a.mode != MODE_REROUTE && resident_shape(a.n_k, a.k + a.m) != 0)
+    const bool led = a.mode != MODE_FULL;
+    if (a.mode != MODE_REROUTE && resident_shape(a.n_k, a.k, a.m, led ? a.r : 0, led ? a.n_sink + a.n_recent : 0) != 0)
         return launch_resident(a, dtype, stream);
     switch (a.mode) {
     case MODE_FULL: return dtype == 0 ? launch_route_f32_full(a, grid, stream) : launch_route_bf16_full(a, grid, stream);
