@@ -152,7 +152,6 @@ constexpr int kQB = 1;              // 32-query blocks per wave (each K / V oper
 constexpr int kAW = kQT / (32 * kQB);  // waves (two per SIMD)
 constexpr int kAT = 64 * kAW;       // threads
 constexpr int kKB = 64;             // keys per staged sub-block
-constexpr int kWaitVmem = 0x0F70;   // s_waitcnt vmcnt(0), the other counters left alone
 constexpr float kLazy = 8.f;        // log2 headroom of the running softmax maximum
 
 template <int D>
@@ -332,10 +331,6 @@ __global__ __launch_bounds__(kAT) void sparse_attention_kernel(AttnArgs a)
         st.load(Kh, Vh, u0, u1, tid);
         st.store(smem, tid);
     }
-    // The query fragments are complete from here on: left pending, they would
-    // put a wait on the vector-memory counter before the score products of
-    // every iteration, and with it one for the sub-block just requested.
-    __builtin_amdgcn_s_waitcnt(kWaitVmem);
     __syncthreads();
 
     for (int it = 0; cur.ci < n_ch; ++it) {
@@ -388,7 +383,7 @@ __global__ __launch_bounds__(kAT) void sparse_attention_kernel(AttnArgs a)
                 float mx = sc[qb][0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[qb][r]);
-                mx = fmaxf(mx, __uint_as_float(xor32(__float_as_uint(mx), lane))) * c2;
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
                 const bool bump = mx > m_run[qb] + kLazy;
                 if (__ballot(bump) != 0ull) {  // (wave-uniform) some query of the wave moves its maximum
                     const float m_new = bump ? mx : m_run[qb];
