@@ -19,9 +19,12 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librouterelay.so")
 SOURCES = ["rr_api.hip", "rr_route.hip", "rr_rescore.hip", "rr_rescore_dense.hip", "rr_consumer.hip"] + [
     f"rr_route_{t}_{m}.hip" for t in ("f32", "bf16") for m in ("full", "anchor", "reroute", "relay")]
-# the resident-score kernel: one object per caller, input type and width
-RESIDENT = [(mode, dt, d) for mode in ("MODE_FULL", "MODE_ANCHOR", "MODE_RELAY")
-            for dt, widths in (("float", (32, 64, 128)), ("bf16_t", (32, 64, 128, 256))) for d in widths]
+# the resident-score kernel: one object per caller, input type and width, all from
+# rr_resident_inst.hip; each is listed under the name its object takes
+RESIDENT = {f"rr_resident_inst_{mode}_{dt}_{d}.hip": (f"-DRR_MODE={mode}", f"-DRR_DT={dt}", f"-DRR_D={d}")
+            for mode in ("MODE_FULL", "MODE_ANCHOR", "MODE_RELAY")
+            for dt, widths in (("float", (32, 64, 128)), ("bf16_t", (32, 64, 128, 256))) for d in widths}
+SOURCES += RESIDENT
 # ... whose atomics come from one lane per wave or from lanes with different
 # addresses: the compiler's wave-level aggregation would only add a wait for the
 # returned value right behind each of them
@@ -39,11 +42,12 @@ FLAGS = [
 ]
 
 
-def _compile(job) -> str:
-    src, defines = job
-    name = "_".join([os.path.splitext(src)[0], *(d.split("=")[1] for d in defines if d.startswith("-D"))])
-    obj = os.path.join(BUILD, name + ".o")
-    cmd = [HIPCC, *FLAGS, *defines, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(name: str) -> str:
+    obj = os.path.join(BUILD, os.path.splitext(name)[0] + ".o")
+    src, more = name, ()
+    if name in RESIDENT:
+        src, more = "rr_resident_inst.hip", RESIDENT[name] + NO_ATOMIC_OPT
+    cmd = [HIPCC, *FLAGS, *more, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
@@ -52,11 +56,8 @@ def _compile(job) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    jobs = [(s, ()) for s in SOURCES]
-    jobs += [("rr_resident_inst.hip", (f"-DRR_MODE={m}", f"-DRR_DT={t}", f"-DRR_D={d}", *NO_ATOMIC_OPT))
-             for m, t, d in RESIDENT]
     with ThreadPoolExecutor(max_workers=16) as ex:
-        objs = list(ex.map(_compile, jobs))
+        objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
