@@ -315,7 +315,8 @@ RelayPlan relay_plan(const rr_config &c)
     RelayPlan p;
     p.bm_words = relay_bm_words(c.n_k);
     const bool split = (c.options & RR_OPT_SPLIT_RELAY) != 0;
-    p.resident = !split && rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0;
+    p.resident = !split && rr::resident_shape(c.dtype, c.d, c.n_heads, c.n_q, c.n_k, c.causal != 0, c.k, c.m, c.r,
+                                                c.n_sink + c.n_recent) != 0;
     const bool fits = p.bm_words <= rr::route_relay_max_bm_words(c.dtype, c.d, c.k + c.m);
     rr::rescore_geometry(rows_of(c), c.n_q, c.n_k, p.geo);
     p.fused = p.resident || (fits && ((c.options & RR_OPT_ONE_PASS_RELAY) || (!split && c.causal)));

@@ -120,7 +120,7 @@ bool route_supported(int dtype, int d, int T);
 // configuration, as 100 * (panels, if several) + 10 * waves + stages,
 // or 0 where it does not apply.  k + m chunks are selected per row, r and
 // n_mand sentinels follow (0 for full routing).
-int resident_shape(int n_k, int k, int m, int r, int n_mand);
+int resident_shape(int dtype, int d, int n_heads, int n_q, int n_k, bool causal, int k, int m, int r, int n_mand);
 int route_tile_rows(int T, int n_heads, int n_q);  // query rows per route tile for T = k + m
 // Largest ledger bitmap (word pairs per row) a relay tile holds in LDS.
 int route_relay_max_bm_words(int dtype, int d, int T);

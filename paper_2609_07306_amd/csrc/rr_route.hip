@@ -40,16 +40,34 @@ constexpr int kPanelSlots = 440;
 
 // The resident-score kernel holds a 32-row tile's scores over the whole key
 // range in registers: up to 1024 keys on four waves, 2048 on eight, and 4096 in
-// panels on eight (causal 32 x 4096 anchor and two relays: 2653 us by two-sweep
-// tiles, 2018 us).  Eight
+// panels on eight (causal 32 x 4096 anchor and two relays at T = 96: 2653 us by
+// two-sweep tiles, 2018 us).  Eight
 // lanes per row (four waves) sort 64 scores, sixteen sort 128.
-int resident_shape(int n_k, int k, int m, int r, int n_mand)
+//
+// Panels pay where the two-sweep tiles are not at their best.  With bf16 rows of
+// up to 256 bytes and enough work for 128-row tiles (T <= 64) those read each key
+// a quarter as often: 32 heads x 1024 x 4096 keys, anchor and relays, 969 us
+// against 1254 in panels; causal 32 x 4096 1138 against 1652.  With few of them
+// panels win: 16 heads x 1024 x 4096 415 against 319 us.  Wider routes (64-row
+// tiles) without the causal mask relay by rescoring and a compacted reroute,
+// which at a low drift is the faster way where rows are many (32 x 4096, 9 % of
+// the rows rerouted: 1796 against 2592 us; 32 x 1024: 649 against 668).  Binary32
+// and 512-byte rows: 2874 against 1305 us and 1050 against 848 at 32 x 1024 x 4096.
+static bool panels_pay(int dtype, int d, int n_heads, int n_q, bool causal, int T)
+{
+    if (dtype == 0 || d > 128) return true;
+    if (T <= 64) return (int64_t)n_heads * ((n_q + kNarrowTileRows - 1) / kNarrowTileRows) < kFewTiles;
+    return causal || (int64_t)n_heads * ((n_q + kWideTileRows - 1) / kWideTileRows) < 2 * kFewTiles;
+}
+
+int resident_shape(int dtype, int d, int n_heads, int n_q, int n_k, bool causal, int k, int m, int r, int n_mand)
 {
     const int T = k + m;
     if (n_k > 4096 || T > 128) return 0;
     if (n_k > 2048) {
         const auto up = [](int x) { return (x + 3) & ~3; };
-        return up(k) + up(m + r + n_mand) + up(r) <= kPanelSlots ? 386 : 0;
+        const bool fits = up(k) + up(m + r + n_mand) + up(r) <= kPanelSlots;
+        return fits && panels_pay(dtype, d, n_heads, n_q, causal, T) ? 386 : 0;
     }
     const int nw = (T > 64 || n_k > 1024) ? 8 : 4;
     const int kt = n_k <= 64 * nw ? 2 : (n_k <= 128 * nw ? 4 : 8);
@@ -113,7 +131,8 @@ hipError_t launch_resident(const RouteArgs &a, int dtype, hipStream_t stream)
 hipError_t launch_route(const RouteArgs &a, int dtype, int grid, hipStream_t stream)
 {
     const bool led = a.mode != MODE_FULL;
-    if (a.mode != MODE_REROUTE && resident_shape(a.n_k, a.k, a.m, led ? a.r : 0, led ? a.n_sink + a.n_recent : 0) != 0)
+    if (a.mode != MODE_REROUTE && resident_shape(dtype, a.d, a.n_heads, a.n_q, a.n_k, a.causal != 0, a.k, a.m, led ? a.r : 0,
+                                                 led ? a.n_sink + a.n_recent : 0) != 0)
         return launch_resident(a, dtype, stream);
     switch (a.mode) {
     case MODE_FULL: return dtype == 0 ? launch_route_f32_full(a, grid, stream) : launch_route_bf16_full(a, grid, stream);
