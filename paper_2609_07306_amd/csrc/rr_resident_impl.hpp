@@ -36,9 +36,8 @@
 //      most the T-th score; a few bisection steps over the maxima, 2 NW
 //      adjacent lanes per row (DPP reductions), give a v that few more than T
 //      scores reach.
-//   2. collection: a lane counts its scores >= v from the sign bits of the
-//      differences, takes its place in the row's list by one LDS add, and
-//      appends (score, id) in any order.  A row with more candidates than its
+//   2. collection: a lane counts its scores >= v, takes its place in the row's
+//      list by one LDS add, and appends (score, id) in any order.  A row with more candidates than its
 //      list holds raises v by bisection on the order-preserving integer image
 //      of the scores, then cuts its ties by id: counts over registers, every
 //      wave following all 32 rows.
@@ -270,6 +269,32 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
+
+// Those of a lane's 16 scores that reach th, by the compare instruction that
+// append16 admits by: the count sizes the place a lane takes in its row's list,
+// so the two agree on every pair of floats.  (The sign of s - th, also two
+// operations a score, does not: -0 - +0 is -0, and a NaN has either sign.)
+// Four compares go to scalar masks before the first is read, as a carry; each
+// of the four adds to a count of its own.
+struct Count4 {
+    int n[4] = {0, 0, 0, 0};
+    __device__ __forceinline__ void add(const f32x16_t &s, float th)
+    {
+#define RR_CMP(m) "v_cmp_ge_f32_e64 %[m" #m "], %[x" #m "], %[th]\n\t"
+#define RR_ADD(m) "v_addc_co_u32_e64 %[n" #m "], %[m" #m "], 0, %[n" #m "], %[m" #m "]\n\t"
+#pragma unroll
+        for (int b = 0; b < 16; b += 4) {
+            uint64_t m0, m1, m2, m3;
+            asm(RR_CMP(0) RR_CMP(1) RR_CMP(2) RR_CMP(3) RR_ADD(0) RR_ADD(1) RR_ADD(2) RR_ADD(3)
+                : [n0] "+v"(n[0]), [n1] "+v"(n[1]), [n2] "+v"(n[2]), [n3] "+v"(n[3]), [m0] "=&s"(m0), [m1] "=&s"(m1),
+                  [m2] "=&s"(m2), [m3] "=&s"(m3)
+                : [x0] "v"(s[b]), [x1] "v"(s[b + 1]), [x2] "v"(s[b + 2]), [x3] "v"(s[b + 3]), [th] "v"(th));
+        }
+#undef RR_ADD
+#undef RR_CMP
+    }
+    __device__ __forceinline__ int sum() const { return n[0] + n[1] + n[2] + n[3]; }
+};
 
 // Appends those of a lane's 16 scores that reach th to LDS as (score, id)
 // pairs from byte `at`, with the id of score i = id + i.  The compares of
@@ -775,16 +800,12 @@ void resident_kernel(RouteArgs a)
                     cnt += (ties ? (xs[j] > th) | ((xs[j] == th) & ((int)xi[j] <= th_id)) : xs[j] >= th) ? 1 : 0;
             }
             if (!ties) {
+                Count4 c4;
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {
-                    if (st < nb) {
-                        uint32_t below = 0;  // sign bits of s - th (masked scores are -inf, th is above)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            below = __builtin_amdgcn_alignbit(below, __float_as_uint(acc[st][i] - th), 31);
-                        cnt += 16 - __popc(below);
-                    }
+                    if (st < nb) c4.add(acc[st], th);  // (masked scores are -inf, th is above)
                 }
+                cnt += c4.sum();
             } else {
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {

@@ -1,0 +1,93 @@
+"""Scores at the ends of binary32 through the resident-score route kernel, one
+panel of keys and several: zeros of both signs, NaN.
+
+The inputs are scaled unit vectors or constants, so that every score is known
+exactly; the expected routes are the k highest scores, -0 equal to +0, ties to
+the lower id."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    torch.cuda.set_device(0)
+    yield
+
+
+def _top(scores, width):
+    """Ids of the `width` highest scores of each row, highest first (equal: lower id)."""
+    return np.argsort(-scores, axis=1, kind="stable")[:, :width]
+
+
+def _expected(scores, k, m):
+    ids = _top(scores, k + m)
+    return np.sort(ids[:, :k], axis=1), np.sort(ids[:, k:k + m], axis=1)
+
+
+def _check_routing(Q, K, scores, k, m, r, dtype="f32"):
+    """Full routing, an anchor, and a relay that refreshes every row, against
+    the exact scores [n, n_k] of one head."""
+    from parity_util import dev, ledger_np
+    from paper_2609_07306_amd import routerelay as rr
+    from paper_2609_07306_amd import synth
+    n, nk, d = Q.shape[1], K.shape[1], Q.shape[2]
+    as_dev = lambda x: dev(synth.bf16_round(x) if dtype == "bf16" else x, dtype)  # noqa: E731
+    Qd, Kd = as_dev(Q), as_dev(K)
+    R, N = _expected(scores, k, m)
+    full = torch.full((n, k), -7, dtype=torch.int32, device="cuda")
+    fs = torch.zeros(n, k, device="cuda")
+    rr.full_route(rr.Config(1, 1, n, nk, d, k, 0, 0, dtype), Qd, Kd, full, scores=fs)
+    np.testing.assert_array_equal(full.cpu().numpy(), R, err_msg="full")
+    np.testing.assert_array_equal(fs.cpu().numpy(), np.take_along_axis(scores, R, 1), err_msg="scores")
+    led = rr.Ledger(rr.Config(1, 1, n, nk, d, k, m, r, dtype, gamma=np.inf))
+    for what in ("anchor", "relay"):
+        out = torch.full((n, k), -7, dtype=torch.int32, device="cuda")
+        if what == "anchor":
+            led.anchor(0, Qd, Kd, routes=out)
+        else:
+            mask = torch.zeros(n, dtype=torch.uint8, device="cuda")
+            led.relay(1, Qd, Kd, routes=out, mask=mask)
+            assert bool(mask.all())
+        got = ledger_np(led)
+        np.testing.assert_array_equal(out.cpu().numpy(), R, err_msg=f"{what}: routes out")
+        np.testing.assert_array_equal(got["routes"], R, err_msg=f"{what}: ledger routes")
+        np.testing.assert_array_equal(got["sent"][:, :m], N, err_msg=f"{what}: near misses")
+        draws = got["sent"][:, m:]
+        assert ((draws >= 0) & (draws < nk)).all(), what
+        assert all(len(set(a) | set(b)) == k + m + r for a, b in zip(got["sent"], R)), what
+    led.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nk", [256, 2304])
+def test_zeros_of_both_signs(nk, dtype):
+    """Products that underflow to -0 beside +0: every second block of 16 keys.
+    The blocks are a stage apart, so each kept maximum is a +0 and so is the
+    row's threshold, which the -0 scores reach as well."""
+    n, d, k, m, r = 40, 32, 40, 20, 8
+    Q = np.full((1, n, d), 2.0 ** -100, np.float32)
+    K = np.zeros((1, nk, d), np.float32)
+    K[0, (np.arange(nk) >> 4) % 2 == 1] = -2.0 ** -100
+    s = np.zeros((n, nk), np.float32)
+    _check_routing(Q, K, s, k, m, r, dtype)
+
+
+@pytest.mark.parametrize("nk", [700, 2304])
+def test_nan_scores_are_not_routed(nk):
+    """Chunks whose representation holds a NaN: no row routes to them while it
+    has others, and every id handed out is one of the head's chunks."""
+    n, d, k, m, r = 40, 32, 30, 10, 16
+    rng = np.random.default_rng(nk)
+    Q = rng.integers(-2, 3, size=(1, n, d)).astype(np.float32)
+    Q[:, :, 0] = 1.0
+    K = rng.integers(-1, 2, size=(1, nk, d)).astype(np.float32)
+    s = (Q[0] @ K[0].T).astype(np.float32)  # small integers: exact
+    bad = rng.choice(nk, nk // 7, replace=False)
+    K[0, bad, 0] = np.where(np.arange(len(bad)) % 2, np.nan, -np.nan)
+    s[:, bad] = -1e30
+    _check_routing(Q, K, s, k, m, r)
