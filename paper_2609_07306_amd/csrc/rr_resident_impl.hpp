@@ -72,6 +72,7 @@ using route_detail::static_for;
 using route_detail::transposed_row;
 
 constexpr int kBoundRounds = 3;  // times the bound's range is cut into levels, at most
+constexpr float kLeastSpan = 0x1p-100f, kMostSpan = 0x1p120f;  // widths of a range that is cut into levels
 constexpr float kLowest = -FLT_MAX;  // threshold that admits every valid score (masked keys hold -inf)
 
 template <typename DT, int D, int NW, int KT, int P>
@@ -713,14 +714,18 @@ void resident_kernel(RouteArgs a)
         // highest level that T of them reach.  A level holds the maxima within
         // half a step of it however the conversion rounds, so its bound lies
         // 0.51 steps below.  Where much of the row falls into one level (an
-        // outlier stretches the range) that level is cut again.
+        // outlier stretches the range) that level is cut again.  A range whose
+        // width or its reciprocal leaves the normal floats is not cut: its
+        // levels would come out as infinities and NaN.  lo then stays where it
+        // is, a lower bound still, and the collection raises it.
         float lo = nfin >= T ? umin : kLowest, hi = rmax;
         if (P > 1 && p > 0) lo = fmaxf(lo, th_s[sr]);
         int clo = nfin;
         for (int it = 0; it < kBoundRounds; ++it) {
-            const bool go = on & (nfin >= T) & (clo > T + (T >> 3)) & (hi > lo);
+            const float span = hi - lo;
+            const bool go = on & (nfin >= T) & (clo > T + (T >> 3)) & (span > kLeastSpan) & (span < kMostSpan);
             if (__ballot(go) == 0ull) break;
-            const float step = (hi - lo) * (1.0f / 127.0f), inv = 127.0f * __builtin_amdgcn_rcpf(hi - lo);
+            const float step = span * (1.0f / 127.0f), inv = 127.0f * __builtin_amdgcn_rcpf(span);
             uint32_t x[NU / 4];
 #pragma unroll
             for (int q = 0; q < NU / 4; ++q) {

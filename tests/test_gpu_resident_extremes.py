@@ -1,5 +1,5 @@
 """Scores at the ends of binary32 through the resident-score route kernel, one
-panel of keys and several: zeros of both signs, NaN.
+panel of keys and several: zeros of both signs, NaN, a range wider than the largest float.
 
 The inputs are scaled unit vectors or constants, so that every score is known
 exactly; the expected routes are the k highest scores, -0 equal to +0, ties to
@@ -90,4 +90,32 @@ def test_nan_scores_are_not_routed(nk):
     bad = rng.choice(nk, nk // 7, replace=False)
     K[0, bad, 0] = np.where(np.arange(len(bad)) % 2, np.nan, -np.nan)
     s[:, bad] = -1e30
+    _check_routing(Q, K, s, k, m, r)
+
+
+def _column(nk, values):
+    """Keys whose only component is `values`: a query (q, 0, ...) scores q * values."""
+    K = np.zeros((1, nk, 32), np.float32)
+    K[0, :, 0] = values
+    return K
+
+
+def _queries(n, q):
+    Q = np.zeros((1, n, 32), np.float32)
+    Q[0, :, 0] = q
+    return Q
+
+
+@pytest.mark.parametrize("nk", [100, 600, 2304])
+def test_finite_scores_wider_than_the_largest_float(nk):
+    """Rows whose highest and lowest scores lie further apart than the largest
+    finite float, the highest T close together or not."""
+    n, k, m, r = 40, 30, 10, 8
+    rng = np.random.default_rng(nk)
+    v = np.where(rng.random(nk) < 0.5, 1.0, -1.0) * (2e38 + 1e32 * rng.permutation(nk))
+    v[::7] *= 1e-3
+    q = np.where(np.arange(n) % 3 == 0, -1.0, 1.0) * np.where(np.arange(n) % 5 == 0, 1e-38, 1.0)
+    K, Q = _column(nk, v.astype(np.float32)), _queries(n, q.astype(np.float32))
+    s = Q[0, :, :1] * K[0, :, 0][None, :]
+    assert np.isfinite(s).all()
     _check_routing(Q, K, s, k, m, r)
