@@ -74,6 +74,12 @@ using route_detail::transposed_row;
 constexpr int kBoundRounds = 3;  // times the bound's range is cut into levels, at most
 constexpr float kLeastSpan = 0x1p-100f, kMostSpan = 0x1p120f;  // widths of a range that is cut into levels
 constexpr float kLowest = -FLT_MAX;  // threshold that admits every valid score (masked keys hold -inf)
+// What th_s holds in place of a threshold's bits.  Every float is a threshold
+// that a row may have, +inf too, so these are bits of NaN, and as such they are
+// only compared as integers.
+constexpr uint32_t kNotRouted = 0xFFFFFFFFu;  // the row is not routed by this launch
+constexpr uint32_t kStopped = 0xFFFFFFFEu;    // it stopped at the sweep cap in an earlier panel: no candidate
+constexpr uint32_t kNoScore = 0x7FC00000u;    // a threshold (NaN) that v_cmp_ge finds no score to reach
 
 template <typename DT, int D, int NW, int KT, int P>
 struct Shape {
@@ -271,7 +277,7 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-// Those of a lane's 16 scores that reach th, by the compare instruction that
+// Those of a lane's scores that reach th (a float's bits), by the compare instruction that
 // append16 admits by: the count sizes the place a lane takes in its row's list,
 // so the two agree on every pair of floats.  (The sign of s - th, also two
 // operations a score, does not: -0 - +0 is -0, and a NaN has either sign.)
@@ -279,12 +285,14 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p)
 // of the four adds to a count of its own.
 struct Count4 {
     int n[4] = {0, 0, 0, 0};
-    __device__ __forceinline__ void add(const f32x16_t &s, float th)
+    template <int N = 16, class X>
+    __device__ __forceinline__ void add(const X &s, uint32_t th)
     {
+        static_assert(N % 4 == 0, "groups of four");
 #define RR_CMP(m) "v_cmp_ge_f32_e64 %[m" #m "], %[x" #m "], %[th]\n\t"
 #define RR_ADD(m) "v_addc_co_u32_e64 %[n" #m "], %[m" #m "], 0, %[n" #m "], %[m" #m "]\n\t"
 #pragma unroll
-        for (int b = 0; b < 16; b += 4) {
+        for (int b = 0; b < N; b += 4) {
             uint64_t m0, m1, m2, m3;
             asm(RR_CMP(0) RR_CMP(1) RR_CMP(2) RR_CMP(3) RR_ADD(0) RR_ADD(1) RR_ADD(2) RR_ADD(3)
                 : [n0] "+v"(n[0]), [n1] "+v"(n[1]), [n2] "+v"(n[2]), [n3] "+v"(n[3]), [m0] "=&s"(m0), [m1] "=&s"(m1),
@@ -305,7 +313,7 @@ struct Count4 {
 // compare straight into the execution mask waits for it: 58).  Every lane of
 // the wave is active.  The writes are complete only after a wait on the LDS
 // counter, which is the caller's.
-__device__ __forceinline__ void append16(const f32x16_t &s, float th, uint32_t &at, uint32_t id)
+__device__ __forceinline__ void append16(const f32x16_t &s, uint32_t th, uint32_t &at, uint32_t id)
 {
 #define RR_CMP(m, x) "v_cmp_ge_f32_e64 %[m" #m "], %[x" #m "], %[th]\n\t"
 #define RR_APP(m, i) \
@@ -336,7 +344,7 @@ __device__ __forceinline__ void append16(const f32x16_t &s, float th, uint32_t &
 
 // The same for N (a multiple of four) scores with an id each.
 template <int N>
-__device__ __forceinline__ void append_listed(const float (&x)[N], const uint32_t (&id)[N], float th, uint32_t &at)
+__device__ __forceinline__ void append_listed(const float (&x)[N], const uint32_t (&id)[N], uint32_t th, uint32_t &at)
 {
     static_assert(N % 4 == 0, "groups of four");
 #define RR_CMP(m) "v_cmp_ge_f32_e64 %[m" #m "], %[x" #m "], %[th]\n\t"
@@ -375,7 +383,8 @@ void resident_kernel(RouteArgs a)
     using S = Shape<DT, D, NW, KT, P>;
     constexpr int LPR = S::LPR, RPW = S::RPW, CAP = S::CAP;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ float th_s[32], rmax_s[32];
+    __shared__ uint32_t th_s[32];
+    __shared__ float rmax_s[32];
     __shared__ int32_t row_cnt[3][32], row_c[32];
     __shared__ float2 ab_s[NW][32];
     __shared__ unsigned long long s_pairs;
@@ -719,7 +728,10 @@ void resident_kernel(RouteArgs a)
         // levels would come out as infinities and NaN.  lo then stays where it
         // is, a lower bound still, and the collection raises it.
         float lo = nfin >= T ? umin : kLowest, hi = rmax;
-        if (P > 1 && p > 0) lo = fmaxf(lo, th_s[sr]);
+        if (P > 1 && p > 0) {
+            const uint32_t before = th_s[sr];
+            if (before < kStopped) lo = fmaxf(lo, __uint_as_float(before));
+        }
         int clo = nfin;
         for (int it = 0; it < kBoundRounds; ++it) {
             const float span = hi - lo;
@@ -755,8 +767,8 @@ void resident_kernel(RouteArgs a)
             }
         }
         if (part == 0) {
-            th_s[sr] = (on & !dead) ? lo : INFINITY;
-            rmax_s[sr] = P > 1 ? (on ? (dead ? INFINITY : rmax) : 0.f) : rmax;
+            th_s[sr] = on ? (dead ? kStopped : __float_as_uint(lo)) : kNotRouted;
+            rmax_s[sr] = rmax;
         }
     }
     lds_barrier();
@@ -768,13 +780,16 @@ void resident_kernel(RouteArgs a)
 
     // ------------------------------------------- collection into row lists
     // (every wave follows all 32 rows: lane (l32, hh) holds row l32's state)
-    float th = th_s[l32];
-    routed = P > 1 ? (th < INFINITY) | (rmax_s[l32] == INFINITY) : th < INFINITY;
+    // (the threshold is kept as bits: kNoScore must not meet float arithmetic)
+    uint32_t th = th_s[l32];
+    bool live = th < kStopped;  // the row collects
+    routed = th != kNotRouted;
+    th = live ? th : kNoScore;
     const int nv = last ? myn : min(myn, kp + 32 * NW * nb);  // the row's valid keys so far
     int base = 0, cnt = 0;
     {
         int th_id = INT_MAX, state = 0, id_lo = -1, id_hi = 0;  // state 1: cutting ties at th by id
-        uint32_t lk = float_order(th), hk = float_order(rmax_s[l32]) + 1u;
+        uint32_t lk = float_order(__uint_as_float(th)), hk = float_order(rmax_s[l32]) + 1u;
         bool settled = true, ties = false;
         int total = 0;
         // the candidates so far, rewritten with this panel's: every 2 NW-th is this lane's
@@ -797,28 +812,35 @@ void resident_kernel(RouteArgs a)
                 }
             }
         }
+        // ties: a score is admitted above tf, or at it by its id (none of a row that does not collect)
+        auto tie_score = [&]() { return __uint_as_float(live ? th : 0x7F800000u); };
+        auto tie_cut = [&]() { return live ? th_id : -1; };
         for (int it = 0;; ++it) {
             cnt = 0;
-            if (more_lists) {
-#pragma unroll
-                for (int j = 0; j < NX; ++j)
-                    cnt += (ties ? (xs[j] > th) | ((xs[j] == th) & ((int)xi[j] <= th_id)) : xs[j] >= th) ? 1 : 0;
-            }
             if (!ties) {
                 Count4 c4;
+                if constexpr (P > 1) {
+                    if (more_lists) c4.template add<NX>(xs, th);
+                }
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {
                     if (st < nb) c4.add(acc[st], th);  // (masked scores are -inf, th is above)
                 }
                 cnt += c4.sum();
             } else {
+                const float tf = tie_score();
+                const int tid_cut = tie_cut();
+                if (more_lists) {
+#pragma unroll
+                    for (int j = 0; j < NX; ++j) cnt += ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) ? 1 : 0;
+                }
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {
                     if (st < nb) {
-                        const int lim = th_id - (kbase + 16 * st);
+                        const int lim = tid_cut - (kbase + 16 * st);
 #pragma unroll
                         for (int i = 0; i < 16; ++i)
-                            cnt += ((acc[st][i] > th) | ((acc[st][i] == th) & (i <= lim))) ? 1 : 0;
+                            cnt += ((acc[st][i] > tf) | ((acc[st][i] == tf) & (i <= lim))) ? 1 : 0;
                     }
                 }
             }
@@ -830,11 +852,11 @@ void resident_kernel(RouteArgs a)
             bool again = false;
             // the row's least admissible count (T_i <= T; rows not routed admit nothing)
             if (it == 0) {
-                const bool few = (th < INFINITY) & (total < min(a.k + a.m, nv));
+                const bool few = live & (total < min(a.k + a.m, nv));
                 if (__ballot((total > CAP) | few) == 0ull) break;  // the usual case
                 if (few) lk = float_order(kLowest);  // (the bound's rounding overshot: not a lower bound)
             }
-            if (th < INFINITY) {
+            if (live) {
                 const int ki = a.k_rows ? min(max(a.k_rows[g0 + min(l32, nrows - 1)], 1), a.k) : a.k;
                 const int Ti = ki + a.m, need = min(Ti, nv);
                 if (state == 1) {
@@ -851,20 +873,20 @@ void resident_kernel(RouteArgs a)
                         again = true;
                     }
                 } else if (total < need) {
-                    hk = float_order(th);
+                    hk = float_order(__uint_as_float(th));
                     again = true;
                 } else if (total > CAP) {
-                    lk = float_order(th);
+                    lk = float_order(__uint_as_float(th));
                     again = true;
                 }
                 if (state == 0 && again) {
                     if (hk - lk > 1u) {
-                        th = order_float(lk + ((hk - lk) >> 1));
+                        th = __float_as_uint(order_float(lk + ((hk - lk) >> 1)));
                     } else {
                         // lk is the T_i-th score: the chunks above it and the
                         // lowest ids of its ties; bisect the id cut
                         state = 1;
-                        th = order_float(lk);
+                        th = __float_as_uint(order_float(lk));
                         id_lo = -1;
                         id_hi = nv - 1;
                         th_id = -1 + (nv >> 1);
@@ -877,7 +899,8 @@ void resident_kernel(RouteArgs a)
                 // stopped at the cap: the row keeps no candidate
                 settled = !again;
                 if (again) {
-                    th = INFINITY;
+                    live = false;
+                    th = kNoScore;
                     cnt = 0;
                     total = 0;
                 }
@@ -901,10 +924,12 @@ void resident_kernel(RouteArgs a)
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         } else {
             uint2 *lst = reinterpret_cast<uint2 *>(lists + l32 * S::LSTR) + base;
+            const float tf = tie_score();
+            const int tid_cut = tie_cut();
             if (more_lists) {
 #pragma unroll
                 for (int j = 0; j < NX; ++j) {
-                    if ((xs[j] > th) | ((xs[j] == th) & ((int)xi[j] <= th_id))) {
+                    if ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) {
                         *lst = make_uint2(__float_as_uint(xs[j]), xi[j]);
                         ++lst;
                     }
@@ -913,10 +938,10 @@ void resident_kernel(RouteArgs a)
 #pragma unroll
             for (int st = 0; st < KT; ++st) {
                 if (st < nb) {
-                    const int lim = th_id - (kbase + 16 * st);
+                    const int lim = tid_cut - (kbase + 16 * st);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        if ((acc[st][i] > th) | ((acc[st][i] == th) & (i <= lim))) {
+                        if ((acc[st][i] > tf) | ((acc[st][i] == tf) & (i <= lim))) {
                             *lst = make_uint2(__float_as_uint(acc[st][i]), (uint32_t)(kbase + 16 * st + i));
                             ++lst;
                         }

@@ -1,5 +1,6 @@
 """Scores at the ends of binary32 through the resident-score route kernel, one
-panel of keys and several: zeros of both signs, NaN, a range wider than the largest float.
+panel of keys and several: zeros of both signs, NaN, ranges wider than the
+largest float, infinities.
 
 The inputs are scaled unit vectors or constants, so that every score is known
 exactly; the expected routes are the k highest scores, -0 equal to +0, ties to
@@ -118,4 +119,19 @@ def test_finite_scores_wider_than_the_largest_float(nk):
     K, Q = _column(nk, v.astype(np.float32)), _queries(n, q.astype(np.float32))
     s = Q[0, :, :1] * K[0, :, 0][None, :]
     assert np.isfinite(s).all()
+    _check_routing(Q, K, s, k, m, r)
+
+
+@pytest.mark.parametrize("nk,hot", [(100, 50), (600, 45), (600, 500), (2304, 60), (2304, 1500)])
+def test_infinite_scores(nk, hot):
+    """Products that overflow to +inf: as many as a row selects and more, in a
+    row's list or past it, beside rows where the same chunks are finite."""
+    n, k, m, r = 40, 30, 10, 8
+    rng = np.random.default_rng(nk + hot)
+    v = rng.permutation(nk).astype(np.float32)
+    v[rng.choice(nk, hot, replace=False)] = 3e38
+    K, Q = _column(nk, v), _queries(n, np.where(np.arange(n) % 3 == 1, 1.0, 4.0).astype(np.float32))
+    with np.errstate(over="ignore"):
+        s = Q[0, :, :1] * K[0, :, 0][None, :]
+    assert np.isposinf(s[0]).sum() == hot and np.isfinite(s[1]).all()
     _check_routing(Q, K, s, k, m, r)
