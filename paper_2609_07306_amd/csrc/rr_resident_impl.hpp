@@ -73,7 +73,7 @@ using route_detail::transposed_row;
 
 constexpr int kBoundRounds = 3;  // times the bound's range is cut into levels, at most
 constexpr float kLeastSpan = 0x1p-100f, kMostSpan = 0x1p120f;  // widths of a range that is cut into levels
-constexpr float kLowest = -FLT_MAX;  // threshold that admits every valid score (masked keys hold -inf)
+constexpr float kLowest = -FLT_MAX;  // threshold that admits every score but -inf (which masked keys hold, too)
 // What th_s holds in place of a threshold's bits.  Every float is a threshold
 // that a row may have, +inf too, so these are bits of NaN, and as such they are
 // only compared as integers.
@@ -804,7 +804,7 @@ void resident_kernel(RouteArgs a)
             for (int j = 0; j < NX; ++j) {
                 const int e = 2 * w + hh + LPR * j;
                 xs[j] = -INFINITY;
-                xi[j] = 0;
+                xi[j] = INT_MAX;  // (past every id cut)
                 if (e < c1) {
                     const uint2 x = lst[e];
                     xs[j] = __uint_as_float(x.x);
@@ -851,10 +851,13 @@ void resident_kernel(RouteArgs a)
             total = row_cnt[slot][l32];
             bool again = false;
             // the row's least admissible count (T_i <= T; rows not routed admit nothing)
+            bool few = false;
             if (it == 0) {
-                const bool few = live & (total < min(a.k + a.m, nv));
+                few = live & (total < min(a.k + a.m, nv));
                 if (__ballot((total > CAP) | few) == 0ull) break;  // the usual case
-                if (few) lk = float_order(kLowest);  // (the bound's rounding overshot: not a lower bound)
+                // the bound's rounding overshot, or the row has fewer finite scores
+                // than it takes
+                if (few) lk = float_order(-INFINITY);
             }
             if (live) {
                 const int ki = a.k_rows ? min(max(a.k_rows[g0 + min(l32, nrows - 1)], 1), a.k) : a.k;
@@ -881,10 +884,11 @@ void resident_kernel(RouteArgs a)
                 }
                 if (state == 0 && again) {
                     if (hk - lk > 1u) {
-                        th = __float_as_uint(order_float(lk + ((hk - lk) >> 1)));
+                        th = few ? __float_as_uint(kLowest) : __float_as_uint(order_float(lk + ((hk - lk) >> 1)));
                     } else {
                         // lk is the T_i-th score: the chunks above it and the
-                        // lowest ids of its ties; bisect the id cut
+                        // lowest ids of its ties; bisect the id cut.  (Ties at
+                        // -inf: the masked keys' ids lie past the valid ones.)
                         state = 1;
                         th = __float_as_uint(order_float(lk));
                         id_lo = -1;
@@ -906,7 +910,22 @@ void resident_kernel(RouteArgs a)
                 }
                 break;
             }
-            ties = __ballot(state == 1) != 0ull;
+            if (!ties & (__ballot(state == 1) != 0ull)) {
+                ties = true;
+                // ties are cut by compares that the compiler may turn round (scores
+                // are no NaN to it): a NaN ranks with the -inf ones
+#pragma unroll
+                for (int st = 0; st < KT; ++st) {
+                    if (st < nb) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            float x = acc[st][i];
+                            asm("v_max_f32_e32 %0, 0xff800000, %0" : "+v"(x));
+                            acc[st][i] = x;
+                        }
+                    }
+                }
+            }
         }
         if (w == 0 && hh == 0) {
             row_c[l32] = total;

@@ -53,7 +53,7 @@ def _check_routing(Q, K, scores, k, m, r, dtype="f32"):
         else:
             mask = torch.zeros(n, dtype=torch.uint8, device="cuda")
             led.relay(1, Qd, Kd, routes=out, mask=mask)
-            assert bool(mask.all())
+            assert bool(mask.all()) or not np.isfinite(scores).all()  # (-inf + gamma is not above anything)
         got = ledger_np(led)
         np.testing.assert_array_equal(out.cpu().numpy(), R, err_msg=f"{what}: routes out")
         np.testing.assert_array_equal(got["routes"], R, err_msg=f"{what}: ledger routes")
@@ -78,19 +78,20 @@ def test_zeros_of_both_signs(nk, dtype):
     _check_routing(Q, K, s, k, m, r, dtype)
 
 
-@pytest.mark.parametrize("nk", [700, 2304])
-def test_nan_scores_are_not_routed(nk):
-    """Chunks whose representation holds a NaN: no row routes to them while it
-    has others, and every id handed out is one of the head's chunks."""
+@pytest.mark.parametrize("nk,good", [(700, 600), (700, 12), (2304, 2000), (2304, 0)])
+def test_nan_scores_are_not_routed(nk, good):
+    """Chunks whose representation holds a NaN rank with those of -inf: no row
+    routes to them while it has others, and every id handed out is one of the
+    head's chunks."""
     n, d, k, m, r = 40, 32, 30, 10, 16
     rng = np.random.default_rng(nk)
     Q = rng.integers(-2, 3, size=(1, n, d)).astype(np.float32)
     Q[:, :, 0] = 1.0
     K = rng.integers(-1, 2, size=(1, nk, d)).astype(np.float32)
     s = (Q[0] @ K[0].T).astype(np.float32)  # small integers: exact
-    bad = rng.choice(nk, nk // 7, replace=False)
+    bad = rng.choice(nk, nk - good, replace=False)
     K[0, bad, 0] = np.where(np.arange(len(bad)) % 2, np.nan, -np.nan)
-    s[:, bad] = -1e30
+    s[:, bad] = -np.inf
     _check_routing(Q, K, s, k, m, r)
 
 
@@ -135,3 +136,38 @@ def test_infinite_scores(nk, hot):
         s = Q[0, :, :1] * K[0, :, 0][None, :]
     assert np.isposinf(s[0]).sum() == hot and np.isfinite(s[1]).all()
     _check_routing(Q, K, s, k, m, r)
+
+
+@pytest.mark.parametrize("nk,finite", [(100, 20), (600, 0), (600, 39), (2304, 5), (4096, 0)])
+def test_valid_chunks_of_minus_infinity(nk, finite):
+    """Rows with fewer finite scores than they select (products that overflow to
+    -inf) take the lowest ids of the others, beside rows of finite scores."""
+    n, k, m, r = 40, 30, 10, 8
+    rng = np.random.default_rng(nk + finite)
+    v = np.full(nk, -3e38, np.float32)
+    v[rng.choice(nk, finite, replace=False)] = rng.permutation(finite).astype(np.float32) - 3
+    K, Q = _column(nk, v), _queries(n, np.where(np.arange(n) % 3 == 1, 1.0, 4.0).astype(np.float32))
+    with np.errstate(over="ignore"):
+        s = Q[0, :, :1] * K[0, :, 0][None, :]
+    assert np.isfinite(s[0]).sum() == finite and np.isfinite(s[1]).all()
+    _check_routing(Q, K, s, k, m, r)
+
+
+@pytest.mark.parametrize("n", [300, 2200])
+def test_minus_infinity_under_the_causal_mask(n):
+    """... and never a chunk past the row's position, which the mask also gives -inf."""
+    from paper_2609_07306_amd import routerelay as rr
+    k = 40
+    v = np.full(n, -3e38, np.float32)
+    v[::11] = np.arange(len(v[::11]))
+    Q, K = _queries(n, np.full(n, 4.0, np.float32)), _column(n, v)
+    with np.errstate(over="ignore"):
+        s = np.tile(4.0 * v, (n, 1))
+    routes = torch.full((n, k), -7, dtype=torch.int32, device="cuda")
+    rr.full_route(rr.Config(1, 1, n, n, 32, k, 0, 0, "f32", True), torch.from_numpy(Q).cuda(), torch.from_numpy(K).cuda(),
+                  routes)
+    want = np.full((n, k), -1, np.int32)
+    for i in range(n):
+        ids = np.sort(np.argsort(-s[i, :i + 1], kind="stable")[:k])
+        want[i, :len(ids)] = ids
+    np.testing.assert_array_equal(routes.cpu().numpy(), want)
