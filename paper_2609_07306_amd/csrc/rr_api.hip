@@ -297,12 +297,20 @@ rr::RouteArgs route_args(const rr_config &c, const void *Q, const void *K)
     return a;
 }
 
-// Schedule of a relay layer for a configuration: by default one pass for
-// causal inputs where a tile's ledger bitmaps fit its LDS (compaction would
-// mix short and long causal rows in one tile), else the split schedule,
-// measured faster for non-causal inputs with dense or gathered rescoring;
-// and, for the split schedule with dense rescoring, whether the rescoring
-// pass leaves threshold seeds.
+// Whether the resident-score kernel takes the calls of a mode.
+bool by_resident(const rr_config &c, int mode, bool one_pass)
+{
+    return rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0 &&
+           rr::resident_pays(mode, c.dtype, c.d, c.n_heads, c.n_q, c.n_k, c.causal != 0, c.k + c.m, one_pass);
+}
+
+// Schedule of a relay layer for a configuration: one pass by the
+// resident-score kernel where that is the faster one; else by default one
+// pass over two-sweep tiles for causal inputs where a tile's ledger bitmaps
+// fit its LDS (compaction would mix short and long causal rows in one tile),
+// else the split schedule, measured faster for non-causal inputs with dense or
+// gathered rescoring; and, for the split schedule with dense rescoring,
+// whether the rescoring pass leaves threshold seeds.
 struct RelayPlan {
     bool fused, seeds;
     bool resident;  // the one pass is the resident-score kernel
@@ -314,12 +322,11 @@ RelayPlan relay_plan(const rr_config &c)
 {
     RelayPlan p;
     p.bm_words = relay_bm_words(c.n_k);
-    const bool split = (c.options & RR_OPT_SPLIT_RELAY) != 0;
-    p.resident = !split && rr::resident_shape(c.dtype, c.d, c.n_heads, c.n_q, c.n_k, c.causal != 0, c.k, c.m, c.r,
-                                                c.n_sink + c.n_recent) != 0;
+    const bool split = (c.options & RR_OPT_SPLIT_RELAY) != 0, one_pass = (c.options & RR_OPT_ONE_PASS_RELAY) != 0;
+    p.resident = !split && by_resident(c, rr::MODE_RELAY, one_pass);
     const bool fits = p.bm_words <= rr::route_relay_max_bm_words(c.dtype, c.d, c.k + c.m);
     rr::rescore_geometry(rows_of(c), c.n_q, c.n_k, p.geo);
-    p.fused = p.resident || (fits && ((c.options & RR_OPT_ONE_PASS_RELAY) || (!split && c.causal)));
+    p.fused = p.resident || (fits && (one_pass || (!split && c.causal)));
     p.seeds = !p.fused && p.geo.dense && rr::rescore_dense_seeds(c.dtype, c.d);
     return p;
 }
@@ -417,6 +424,7 @@ rr_status relay_launch(const rr_config &c, const RelayBuffers &b, int32_t layer,
         a.stat_nrr = b.stat_nrr;
         a.pairs_out = pairs;
         a.nrr_out = n_rerouted;
+        a.resident = b.resident;
         if (b.resident) a.routes_out = routes;
         const int grid = c.n_heads * a.tiles_per_head;
         hipError_t e = launch(RR_KERNEL_RELAY, [&] { return rr::launch_route(a, c.dtype, grid, stream); });
@@ -606,6 +614,7 @@ rr_status rr_anchor_route(rr_ledger *L, int32_t layer, const void *Qc, const voi
     a.unconverged = ds->unconverged;
     a.layer = layer;
     a.mode = rr::MODE_ANCHOR;
+    a.resident = by_resident(c, rr::MODE_ANCHOR, false);
     a.routes_out = routes;
     a.led_routes = L->routes;
     a.led_sent = L->sent;
@@ -671,7 +680,15 @@ rr_status rr_relay_layer_static(const rr_config *cfg, int32_t layer, const void 
         return fail(RR_ERR_INVALID, "Qc, Kc and the ledger arrays (routes, sent, build, age) are required");
     if (layer < 0) return fail(RR_ERR_INVALID, "layer must be >= 0");
     RelayPlan plan = relay_plan(c);
-    const StaticLayout lay = static_layout(c, plan);
+    StaticLayout lay = static_layout(c, plan);
+    if (lay.bytes > kScratchBytes && plan.seeds && !(c.options & RR_OPT_SPLIT_RELAY) &&
+        rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0) {
+        // too many rows for the split schedule's threshold seeds: one pass by
+        // the resident-score kernel, the same results without them
+        plan.resident = plan.fused = true;
+        plan.seeds = false;
+        lay = static_layout(c, plan);
+    }
     if (lay.bytes > kScratchBytes)
         return fail(RR_ERR_UNSUPPORTED, "rr_relay_layer_static: the relay scratch of this configuration (" +
                                             std::to_string(lay.bytes) + " bytes) exceeds the library's " +
@@ -727,6 +744,7 @@ rr_status rr_full_route(const rr_config *cfg, const void *Qc, const void *Kc, in
     rr::RouteArgs a = route_args(c, Qc, Kc);
     a.unconverged = ds->unconverged;
     a.mode = rr::MODE_FULL;
+    a.resident = by_resident(c, rr::MODE_FULL, false);
     a.routes_out = routes;
     a.scores_out = route_scores;
     a.pairs_out = pairs;

@@ -64,6 +64,7 @@ struct RouteArgs {
     int64_t *pairs_out;        // optional device scalar
     int64_t pairs_value;       // value written to pairs_out (full / anchor; reroute: the workgroup sums)
     unsigned long long *unconverged;  // device counter: rows whose collection stopped at the sweep cap
+    bool resident;                    // full / anchor / relay: by the resident-score kernel
     bool vec;                         // resident tiles: the outputs' rows may be moved in 16-byte pieces (set by the launcher)
     uint64_t barrett;                 // resident tiles: floor((2^64 - 1) / n_k) (set by the launcher)
     int32_t sweep_cap;                // collection sweeps allowed per tile (kMaxFixIters unless a test lowers it)
@@ -120,12 +121,15 @@ bool route_supported(int dtype, int d, int T);
 // configuration, as 100 * (panels, if several) + 10 * waves + stages,
 // or 0 where it does not apply.  k + m chunks are selected per row, r and
 // n_mand sentinels follow (0 for full routing).
-int resident_shape(int dtype, int d, int n_heads, int n_q, int n_k, bool causal, int k, int m, int r, int n_mand);
+int resident_shape(int n_k, int k, int m, int r, int n_mand);
+// Where it applies, whether it is the faster one for a mode with T = k + m;
+// one_pass: against the two-sweep one-pass relay only, not the split schedule.
+bool resident_pays(int mode, int dtype, int d, int n_heads, int n_q, int n_k, bool causal, int T, bool one_pass);
 int route_tile_rows(int T, int n_heads, int n_q);  // query rows per route tile for T = k + m
 // Largest ledger bitmap (word pairs per row) a relay tile holds in LDS.
 int route_relay_max_bm_words(int dtype, int d, int T);
 hipError_t launch_route(const RouteArgs &a, int dtype, int grid, hipStream_t stream);
-// Full, anchor and relay launches of the resident-score kernel.
+// The launches of the resident-score kernel (RouteArgs::resident).
 hipError_t launch_resident(const RouteArgs &a, int dtype, hipStream_t stream);
 
 }  // namespace rr

@@ -1452,8 +1452,7 @@ template <int MODE, typename DT, int D>
 hipError_t launch_d(const RouteArgs &a, hipStream_t stream)
 {
     const bool led = MODE != MODE_FULL;
-    switch (resident_shape(sizeof(DT) == 4 ? 0 : 1, D, a.n_heads, a.n_q, a.n_k, a.causal != 0, a.k, a.m, led ? a.r : 0,
-                           led ? a.n_sink + a.n_recent : 0)) {
+    switch (resident_shape(a.n_k, a.k, a.m, led ? a.r : 0, led ? a.n_sink + a.n_recent : 0)) {
     case 42: return launch_t<MODE, DT, D, 4, 2>(a, stream);
     case 44: return launch_t<MODE, DT, D, 4, 4>(a, stream);
     case 48: return launch_t<MODE, DT, D, 4, 8>(a, stream);
