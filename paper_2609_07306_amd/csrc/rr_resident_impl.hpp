@@ -305,6 +305,14 @@ struct Count4 {
     __device__ __forceinline__ int sum() const { return n[0] + n[1] + n[2] + n[3]; }
 };
 
+// -inf for a NaN.  (Ties are cut by compares that the compiler may turn round:
+// to it scores are no NaN.)
+__device__ __forceinline__ float no_nan(float x)
+{
+    asm("v_max_f32_e32 %0, 0xff800000, %0" : "+v"(x));
+    return x;
+}
+
 // Appends those of a lane's 16 scores that reach th to LDS as (score, id)
 // pairs from byte `at`, with the id of score i = id + i.  The compares of
 // eight scores go to scalar masks first; then a score takes its mask as the
@@ -839,8 +847,10 @@ void resident_kernel(RouteArgs a)
                     if (st < nb) {
                         const int lim = tid_cut - (kbase + 16 * st);
 #pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            cnt += ((acc[st][i] > tf) | ((acc[st][i] == tf) & (i <= lim))) ? 1 : 0;
+                        for (int i = 0; i < 16; ++i) {
+                            const float x = no_nan(acc[st][i]);
+                            cnt += ((x > tf) | ((x == tf) & (i <= lim))) ? 1 : 0;
+                        }
                     }
                 }
             }
@@ -910,22 +920,7 @@ void resident_kernel(RouteArgs a)
                 }
                 break;
             }
-            if (!ties & (__ballot(state == 1) != 0ull)) {
-                ties = true;
-                // ties are cut by compares that the compiler may turn round (scores
-                // are no NaN to it): a NaN ranks with the -inf ones
-#pragma unroll
-                for (int st = 0; st < KT; ++st) {
-                    if (st < nb) {
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            float x = acc[st][i];
-                            asm("v_max_f32_e32 %0, 0xff800000, %0" : "+v"(x));
-                            acc[st][i] = x;
-                        }
-                    }
-                }
-            }
+            ties = __ballot(state == 1) != 0ull;
         }
         if (w == 0 && hh == 0) {
             row_c[l32] = total;
@@ -960,8 +955,9 @@ void resident_kernel(RouteArgs a)
                     const int lim = tid_cut - (kbase + 16 * st);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        if ((acc[st][i] > tf) | ((acc[st][i] == tf) & (i <= lim))) {
-                            *lst = make_uint2(__float_as_uint(acc[st][i]), (uint32_t)(kbase + 16 * st + i));
+                        const float x = no_nan(acc[st][i]);
+                        if ((x > tf) | ((x == tf) & (i <= lim))) {
+                            *lst = make_uint2(__float_as_uint(x), (uint32_t)(kbase + 16 * st + i));
                             ++lst;
                         }
                     }
