@@ -64,17 +64,22 @@ typedef enum { RR_F32 = 0, RR_BF16 = 1 } rr_dtype;
  * none.  seed keys the random-sentinel probes. */
 /* Options (rr_config.options).  A relay layer (Sec. 3.2) runs as one of two
  * schedules with the same results:
- *   one pass -- over the 128-row (or 64-row) tiles of every head, the tile's
- *     scores rescore its rows' ledgers, the trigger flags rows, and the same
- *     pass routes the flagged ones (possible while a tile's ledger bitmaps
- *     fit its LDS: n_k up to about 2048, d = 256 up to about 1900);
+ *   one pass -- over the row tiles of every head, the tile's scores rescore
+ *     its rows' ledgers, the trigger flags rows, and the same pass routes the
+ *     flagged ones.  Up to 2048 key chunks, and up to 4096 unless a row has
+ *     more than 440 route, sentinel and draw slots, a 32-row tile keeps its
+ *     scores in registers; other tiles sweep the keys twice and hold the
+ *     ledgers as bitmaps in LDS (n_k up to 3072; k + m > 64: 4608; rows of 512
+ *     bytes, d = 128 binary32 or 256 bf16: 3072 with k + m > 64 only);
  *   split -- rescoring and trigger, then the routing of the flagged rows
  *     compacted per head (Sec. 4.2).
- * By default causal inputs take the one pass where it fits (compaction would
- * mix short and long causal rows in one tile) and other inputs the split
- * schedule, measured faster for them.  RR_OPT_SPLIT_RELAY forces the split
- * schedule, RR_OPT_ONE_PASS_RELAY the one pass (RR_ERR_UNSUPPORTED where it
- * does not fit); not both. */
+ * By default the one measured faster for the shape runs: one pass up to 2048
+ * chunks and for causal inputs where it fits, but the split schedule for many
+ * bf16 rows with k + m up to about 52 over more than 1024 chunks, and for
+ * non-causal inputs beyond.  Where most rows keep their route and rows are
+ * many, the split schedule can be the faster one elsewhere too.
+ * RR_OPT_SPLIT_RELAY forces the split schedule, RR_OPT_ONE_PASS_RELAY the one
+ * pass (RR_ERR_UNSUPPORTED where no tile takes it); not both. */
 typedef enum { RR_OPT_SPLIT_RELAY = 1, RR_OPT_ONE_PASS_RELAY = 2 } rr_option;
 
 typedef struct {

@@ -128,6 +128,18 @@ int64_t full_pairs(const rr_config &c)
 // number of pairs apart.
 int relay_bm_words(int n_k) { return 2 * ((n_k + 63) / 64) + 1; }
 
+// Whether a two-sweep tile's LDS holds its rows' ledger bitmaps, and whether
+// the resident-score kernel applies: either serves a one-pass relay.
+bool two_sweep_relay_fits(const rr_config &c)
+{
+    return relay_bm_words(c.n_k) <= rr::route_relay_max_bm_words(c.dtype, c.d, c.k + c.m);
+}
+
+bool resident_applies(const rr_config &c)
+{
+    return rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0;
+}
+
 rr_status validate(const rr_config *c, bool ledger)
 {
     if (!c) return fail(RR_ERR_INVALID, "config is NULL");
@@ -158,8 +170,7 @@ rr_status validate(const rr_config *c, bool ledger)
     if (c->n_heads > 1024) return fail(RR_ERR_UNSUPPORTED, "n_heads must be <= 1024");
     if (rows_of(*c) * (int64_t)(c->k + m + r + 1) >= (int64_t)INT32_MAX || rows_of(*c) * c->d >= (int64_t)INT32_MAX * 8)
         return fail(RR_ERR_UNSUPPORTED, "problem too large for 32-bit row indexing");
-    if (ledger && (c->options & RR_OPT_ONE_PASS_RELAY) &&
-        relay_bm_words(c->n_k) > rr::route_relay_max_bm_words(c->dtype, c->d, c->k + c->m))
+    if (ledger && (c->options & RR_OPT_ONE_PASS_RELAY) && !two_sweep_relay_fits(*c) && !resident_applies(*c))
         return fail(RR_ERR_UNSUPPORTED, "one-pass relay: the ledger bitmaps of a tile exceed its LDS (n_k too large)");
     return RR_OK;
 }
@@ -300,7 +311,7 @@ rr::RouteArgs route_args(const rr_config &c, const void *Q, const void *K)
 // Whether the resident-score kernel takes the calls of a mode.
 bool by_resident(const rr_config &c, int mode, bool one_pass)
 {
-    return rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0 &&
+    return resident_applies(c) &&
            rr::resident_pays(mode, c.dtype, c.d, c.n_heads, c.n_q, c.n_k, c.causal != 0, c.k + c.m, one_pass);
 }
 
@@ -323,8 +334,8 @@ RelayPlan relay_plan(const rr_config &c)
     RelayPlan p;
     p.bm_words = relay_bm_words(c.n_k);
     const bool split = (c.options & RR_OPT_SPLIT_RELAY) != 0, one_pass = (c.options & RR_OPT_ONE_PASS_RELAY) != 0;
-    p.resident = !split && by_resident(c, rr::MODE_RELAY, one_pass);
-    const bool fits = p.bm_words <= rr::route_relay_max_bm_words(c.dtype, c.d, c.k + c.m);
+    const bool fits = two_sweep_relay_fits(c);
+    p.resident = !split && (by_resident(c, rr::MODE_RELAY, one_pass) || (one_pass && !fits && resident_applies(c)));
     rr::rescore_geometry(rows_of(c), c.n_q, c.n_k, p.geo);
     p.fused = p.resident || (fits && (one_pass || (!split && c.causal)));
     p.seeds = !p.fused && p.geo.dense && rr::rescore_dense_seeds(c.dtype, c.d);
@@ -681,8 +692,7 @@ rr_status rr_relay_layer_static(const rr_config *cfg, int32_t layer, const void 
     if (layer < 0) return fail(RR_ERR_INVALID, "layer must be >= 0");
     RelayPlan plan = relay_plan(c);
     StaticLayout lay = static_layout(c, plan);
-    if (lay.bytes > kScratchBytes && plan.seeds && !(c.options & RR_OPT_SPLIT_RELAY) &&
-        rr::resident_shape(c.n_k, c.k, c.m, c.r, c.n_sink + c.n_recent) != 0) {
+    if (lay.bytes > kScratchBytes && plan.seeds && !(c.options & RR_OPT_SPLIT_RELAY) && resident_applies(c)) {
         // too many rows for the split schedule's threshold seeds: one pass by
         // the resident-score kernel, the same results without them
         plan.resident = plan.fused = true;

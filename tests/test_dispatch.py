@@ -67,3 +67,23 @@ def test_a_forced_one_pass_does_not_compare_with_the_split_schedule():
     assert pays(RELAY, BF16, 128, 32, 2048, 1536, False, 48, True)
     assert pays(RELAY, F32, 64, 32, 2048, 2049, False, 48, True)
     assert not pays(RELAY, BF16, 128, 32, 2100, 2100, False, 48, True)
+
+
+@pytest.mark.parametrize("kw,status", [
+    # by the resident tile, where the two-sweep tile's bitmaps end at 1920 (d = 256; binary32 d = 128) ...
+    (dict(n_k=2048, d=256, dtype="bf16"), -1), (dict(n_k=4096, d=128), -1),
+    # ... or 3072 chunks
+    (dict(n_k=4096, d=128, dtype="bf16"), -1),
+    # two-sweep tiles: routes that stage more slots than a tile of several panels holds, wide routes past 4096
+    (dict(n_k=3072, d=128, dtype="bf16", k=1, m=0, r=255), -1), (dict(n_k=4608, d=64, k=64, m=32), -1),
+    # neither
+    (dict(n_k=4097, d=128, dtype="bf16"), -5), (dict(n_k=3073, d=128, dtype="bf16", k=1, m=0, r=255), -5),
+    (dict(n_k=4609, d=64, k=64, m=32), -5),
+])
+def test_one_pass_relays_are_refused_where_no_tile_takes_them(kw, status):
+    """Null pointers are refused (-1) after the configuration (-5) has been
+    looked at, and before anything is launched."""
+    from paper_2609_07306_amd import routerelay as rr
+    cfg = rr.Config(**{**dict(n_heads=2, n_kv_heads=1, n_q=64, n_k=64, d=64, k=8, m=4, r=4, relay="one_pass"), **kw})
+    got = rr.lib.rr_relay_layer_static(ctypes.byref(cfg.c()), 1, *([None] * 11))
+    assert got == status, rr.lib.rr_last_error()

@@ -77,3 +77,16 @@ def test_static_relay_past_the_split_schedules_scratch():
         assert torch.equal(want[key], own[key]), key
     assert torch.equal(out, want["routes"])
     led.close()
+
+
+ONE_PASS = [_w(70, 2000, 256, "bf16", 32, 16, 16, heads=2, kv=1), _w(1024, 3200, 128, "bf16", 32, 16, 16)]
+
+
+@pytest.mark.parametrize("w", ONE_PASS, ids=[f"{w.n}x{w.nk}-d{w.d}" for w in ONE_PASS])
+def test_forced_one_pass_where_only_the_resident_tile_fits(w):
+    from parity_util import step_compare
+    note(w)
+    st = step_compare(w, heads=[0, w.n_heads - 1], relay="one_pass", note=note)
+    # (by the oracle's scores alone 84 of the 140 rows of the d = 256 case's first
+    # layer lie outside the tie bands, which grow with d: 2 d 2^-24 sum |q k|)
+    assert st["compared"] >= 0.55 * st["rows"] and st["rerouted"] > 0
