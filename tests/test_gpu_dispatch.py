@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2609_07306_amd import synth
-from test_dispatch import ANCHOR, BF16, F32, RELAY, pays
+from test_dispatch import ANCHOR, BF16, F32, FULL, RELAY, pays, shape
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +90,74 @@ def test_forced_one_pass_where_only_the_resident_tile_fits(w):
     # (by the oracle's scores alone 84 of the 140 rows of the d = 256 case's first
     # layer lie outside the tie bands, which grow with d: 2 d 2^-24 sum |q k|)
     assert st["compared"] >= 0.55 * st["rows"] and st["rerouted"] > 0
+
+
+TWO_SWEEP = [
+    # one-pass relays over two-sweep tiles: 128-row; 64-row past 4096 chunks; 32-row (more staged slots than
+    # a tile of several panels holds)
+    (_w(2100, 2100, 128, "bf16", 32, 16, 16, causal=True, heads=16, kv=4, rho=0.1), [3, 14], "relay"),
+    (_w(4200, 4200, 64, "bf16", 64, 32, 16, causal=True, heads=2, kv=1, rho=0.1), [1], "relay"),
+    (_w(2100, 2100, 64, "f32", 1, 0, 255, causal=True, heads=1, kv=1), [0], "relay"),
+    # 128-row anchors, split relays, without and (past the bitmaps) with the mask
+    (_w(1024, 4096, 128, "bf16", 32, 16, 16), [0, 31], "rescore"),
+    (_w(4096, 4096, 128, "bf16", 32, 16, 16, causal=True, heads=16, kv=16), [9], "rescore"),
+]
+
+
+@pytest.mark.parametrize("w,heads,kind", TWO_SWEEP,
+                         ids=[f"{w.n}x{w.nk}-T{w.k + w.m}{'-causal' if w.causal else ''}" for w, _, _ in TWO_SWEEP])
+def test_two_sweep_tiles_that_the_resident_tile_leaves(w, heads, kind):
+    from parity_util import step_compare
+    from paper_2609_07306_amd import routerelay as rr
+    applies = shape(w.nk, w.k, w.m, w.r) != 0
+    assert not applies or not (_pays(w, ANCHOR) or _pays(w, RELAY))
+    note(w)
+    rr.profile_start()
+    st = step_compare(w, heads=heads, note=note)
+    launched = {k for k, (_, n) in rr.profile_stop().items() if n}
+    assert launched == {"anchor", "relay"} if kind == "relay" else launched == {"anchor", "rescore", "reroute"}
+    assert st["compared"] >= 0.5 * st["rows"] and st["rerouted"] > 0
+
+
+@pytest.mark.parametrize("nk,k", [(1500, 32), (2100, 48), (4097, 20)])
+def test_full_routing_by_128_row_tiles(nk, k):
+    """Every row of 32 heads, on small integers (scores exact, ties to the lower id)."""
+    from paper_2609_07306_amd import routerelay as rr
+    heads, n, d = 32, 1000, 64
+    assert nk > 4096 or not pays(FULL, BF16, d, heads, n, nk, False, k)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nk)
+    Q, K = (torch.randint(-3, 4, (heads, x, d), generator=g, device="cuda").float() for x in (n, nk))
+    routes = torch.empty(heads * n, k, dtype=torch.int32, device="cuda")
+    scores = torch.empty(heads * n, k, device="cuda")
+    rr.full_route(rr.Config(heads, heads, n, nk, d, k, 0, 0, "bf16"), Q.bfloat16(), K.bfloat16(), routes, scores=scores)
+    for h in range(heads):
+        S = Q[h] @ K[h].t().contiguous()
+        ids = torch.sort(torch.sort(S, dim=1, descending=True, stable=True).indices[:, :k], dim=1).values
+        assert torch.equal(routes[h * n:(h + 1) * n].long(), ids), h
+        assert torch.equal(scores[h * n:(h + 1) * n], torch.gather(S, 1, ids)), h
+
+
+def test_two_sweep_rows_stopped_at_the_cap():
+    """At a cap of one sweep the rows of equal scores keep no candidate and are
+    counted, the others are exact (more chunks than the resident tile takes)."""
+    from paper_2609_07306_amd import routerelay as rr
+    n, nk, k = 33, 4200, 16
+    assert shape(nk, k) == 0
+    Q = torch.zeros(1, n, 32, device="cuda")
+    K = torch.zeros(1, nk, 32, device="cuda")
+    Q[:, ::2, 0] = 1.0
+    K[:, :, 0] = torch.arange(nk, device="cuda") / 64.0
+    routes = torch.empty(n, k, dtype=torch.int32, device="cuda")
+    before = rr.unconverged_rows()
+    try:
+        rr.set_sweep_cap(1)
+        rr.full_route(rr.Config(1, 1, n, nk, 32, k, 0, 0, "f32"), Q, K, routes)
+        torch.cuda.synchronize()
+    finally:
+        rr.set_sweep_cap(0)
+    got = routes.cpu()
+    stopped = (got == -1).all(1)
+    assert rr.unconverged_rows() - before == int(stopped.sum()) and bool(stopped[1::2].all())
+    want = torch.arange(nk - k, nk, dtype=torch.int32)
+    assert all(torch.equal(row, want) for row in got[~stopped])
