@@ -1888,6 +1888,23 @@ hipError_t launch_c(const RouteArgs &a, int grid, hipStream_t stream)
     return launch_t<MODE, typename C::DType, C::DIM, C::NW_, C::KS_, C::TT_, C::NET, C::CAPQ_>(a, grid, stream);
 }
 
+// Ledger bitmap words (R, C pairs per row) that a relay tile's candidate
+// region holds.  Up to 2048 keys every one-pass relay is the resident-score
+// kernel's, so 32- and 128-row relay tiles whose bitmaps end before (20
+// candidates a sub-list: 1920 keys) do not exist.
+template <class C>
+constexpr int relay_bm_capacity()
+{
+    constexpr int words = (C::SS * 4 + C::SI * 2) / 8;
+    return 32 * words > 2048 ? words : 0;
+}
+
+template <typename DT, int D>
+int relay_max_bm_words(int T)
+{
+    return T > 64 ? relay_bm_capacity<WideRT<DT, D>>() : relay_bm_capacity<NarrowRT<DT, D>>();
+}
+
 template <int MODE, typename DT, int D>
 hipError_t launch_d(const RouteArgs &a, int grid, hipStream_t stream)
 {
@@ -1897,17 +1914,12 @@ hipError_t launch_d(const RouteArgs &a, int grid, hipStream_t stream)
     static_assert(SmallRT<DT, D>::SS == NarrowRT<DT, D>::SS && SmallRT<DT, D>::SI == NarrowRT<DT, D>::SI,
                   "small and narrow tiles give a row the same candidate region");
     if (a.k + a.m > 64) return launch_c<MODE, WideRT<DT, D>>(a, grid, stream);
-    if (a.tile_rows == kSmallTileRows) return launch_c<MODE, SmallRT<DT, D>>(a, grid, stream);
-    return launch_c<MODE, NarrowRT<DT, D>>(a, grid, stream);
-}
-
-// Ledger bitmap words (R, C pairs per row) that a relay tile's candidate
-// region holds.
-template <typename DT, int D>
-int relay_max_bm_words(int T)
-{
-    if (T > 64) return (WideRT<DT, D>::SS * 4 + WideRT<DT, D>::SI * 2) / 8;
-    return (NarrowRT<DT, D>::SS * 4 + NarrowRT<DT, D>::SI * 2) / 8;
+    if constexpr (MODE == MODE_RELAY && relay_bm_capacity<NarrowRT<DT, D>>() == 0) {
+        return hipErrorInvalidValue;
+    } else {
+        if (a.tile_rows == kSmallTileRows) return launch_c<MODE, SmallRT<DT, D>>(a, grid, stream);
+        return launch_c<MODE, NarrowRT<DT, D>>(a, grid, stream);
+    }
 }
 
 template <int MODE, typename DT>
