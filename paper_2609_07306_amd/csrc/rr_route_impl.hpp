@@ -1168,7 +1168,8 @@ __global__ __launch_bounds__(64 * NW * KS) void route_kernel(RouteArgs a)
             {
                 CollectEpi epi;
                 const int off = seg_off[myseg][myrow];
-                epi.th = th_s[myrow];
+                // (-0 for a zero: both zeros less -0 have a clear sign, -0 less +0 has not)
+                epi.th = th_s[myrow] == 0.f ? -0.f : th_s[myrow];
                 epi.th_id = th_id[myrow];
                 epi.nrow = nrow;
                 epi.sbase = sbase;

@@ -161,3 +161,21 @@ def test_two_sweep_rows_stopped_at_the_cap():
     assert rr.unconverged_rows() - before == int(stopped.sum()) and bool(stopped[1::2].all())
     want = torch.arange(nk - k, nk, dtype=torch.int32)
     assert all(torch.equal(row, want) for row in got[~stopped])
+
+
+def test_two_sweep_zeros_of_both_signs():
+    """-0 equals +0: every score is a zero, the +0 ones just as many as the
+    threshold sweep keeps (two per register slot of each of four key segments),
+    the others products that underflow to -0.  Ties to the lower id."""
+    from paper_2609_07306_amd import routerelay as rr
+    n, nk, d, k = 40, 4352, 32, 40
+    assert shape(nk, k) == 0
+    Q = torch.full((1, n, d), 2.0 ** -100, device="cuda")
+    K = torch.full((1, nk, d), -2.0 ** -100, device="cuda")
+    stage = torch.arange(nk, device="cuda") % (nk // 4) // 16
+    K[0, (stage == 3) | (stage == 7)] = 0.0
+    routes = torch.empty(n, k, dtype=torch.int32, device="cuda")
+    scores = torch.empty(n, k, device="cuda")
+    rr.full_route(rr.Config(1, 1, n, nk, d, k, 0, 0, "f32"), Q, K, routes, scores=scores)
+    assert bool((scores == 0).all())
+    assert torch.equal(routes.cpu(), torch.arange(k, dtype=torch.int32).expand(n, k))
