@@ -87,7 +87,9 @@ static bool panels_pay(int dtype, int d, int64_t narrow, int64_t wide, bool caus
 //     531 against 750 / 725, 1024 x 2048 438 / 401 against 426 / 412), past it
 //     their candidate lists overflow (T = 56: 1024 x 1536 442 / 392 against 391 /
 //     380; with `most` 770 / 548 against 749 / 729; T = 60 854 / 618 against 728 /
-//     695).  At 1024 keys the tile wins: 549 / 423 against 427 / 417.
+//     695).  At 1024 keys the tile wins: 549 / 423 against 427 / 417.  So do
+//     relays of d = 32 past 1536 keys without `most` (1024 x 1792 321 / 292
+//     against 303 / 284; with it, 2048 x 2048, 609 / 473 against 605 / 568).
 //   bf16, d = 256, more than 512 keys, T <= 24: full routing at k = 8 and 2048 x
 //     1280 167 against 182 us (k = 32: 198 against 183); relays with `most`
 //     only: T = 12, 2048 x 1536 988 / 695 against 960 / 918, 1024 x 1536 522 /
@@ -103,7 +105,7 @@ bool resident_pays(int mode, int dtype, int d, int n_heads, int n_q, int n_k, bo
     const bool relay = mode == MODE_RELAY, many = narrow >= kFewTiles, most = narrow >= 2 * kFewTiles;
     if (causal || T > 64 || !many || (relay && one_pass)) return true;
     if (dtype == 0) return !(relay && most && n_k > 2048 && d <= 64 && T <= 56);
-    if (d <= 128) return n_k <= 1024 || T > (most ? 56 : 52);
+    if (d <= 128) return n_k <= 1024 || T > (most ? 56 : 52) || (relay && !most && d == 32 && n_k > 1536);
     return n_k <= 512 || n_k > 2048 || T > 24 || (relay && !most);
 }
 

@@ -40,6 +40,9 @@ LINES = [
     (RELAY, BF16, 128, 31, 1024, 1280, False, 48, True), (RELAY, BF16, 128, 32, 897, 1280, False, 48, False),
     # ... two per unit, T <= 56
     (RELAY, BF16, 128, 32, 2048, 1536, False, 56, False), (RELAY, BF16, 128, 32, 2048, 1536, False, 57, True),
+    # ... and relays of 64-byte rows only up to 1536 keys without two tiles per unit
+    (RELAY, BF16, 32, 32, 1024, 1536, False, 48, False), (RELAY, BF16, 32, 32, 1024, 1537, False, 48, True),
+    (RELAY, BF16, 32, 32, 2048, 1537, False, 48, False), (ANCHOR, BF16, 32, 32, 1024, 1537, False, 48, False),
     (RELAY, BF16, 128, 32, 2048, 1536, True, 48, True), (RELAY, F32, 128, 32, 2048, 1536, False, 48, True),
     # 512-byte rows: from 513 keys, T <= 24, a relay from two tiles per unit
     (FULL, BF16, 256, 32, 1024, 512, False, 24, True), (FULL, BF16, 256, 32, 1024, 513, False, 24, False),

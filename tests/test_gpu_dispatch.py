@@ -38,7 +38,7 @@ def _pays(w, mode):
 MANY_ROWS = [
     # (workload, anchors by the resident tile)
     (_w(1024, 1025, 128, "bf16", 32, 16, 16), False),
-    (_w(1030, 2047, 32, "bf16", 36, 16, 16, heads=30, kv=15, rho=0.01), False),
+    (_w(1030, 2047, 64, "bf16", 36, 16, 16, heads=30, kv=15, rho=0.01), False),
     (_w(2048, 513, 256, "bf16", 16, 8, 8), False),
     (_w(2000, 2100, 64, "f32", 32, 24, 16, rho=0.02), True),
 ]
