@@ -80,7 +80,7 @@ def parse():
     ap.add_argument("--n", type=int, default=None, help="chunk count override (n_q = n_k)")
     ap.add_argument("--rho", type=float, default=None)
     ap.add_argument("--relay", default="auto", choices=("auto", "one_pass", "split"),
-                    help="relay schedule (auto: one pass for causal inputs, else rescoring + compacted reroute)")
+                    help="relay schedule (auto: the one measured faster for the shape; split: rescoring + compacted reroute)")
     ap.add_argument("--cpu-heads", type=int, default=2, help="heads in the oracle's timed sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-full", action="store_true", help="skip the full-routing baseline")

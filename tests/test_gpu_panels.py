@@ -1,6 +1,6 @@
 """Parity of the resident-score route kernel over several panels of keys (2048 <
 n_k <= 4096) with the oracle: key counts at the ends of the range and of a
-panel, causal tiles either side of the second panel, the widest routes, few and
+panel, causal tiles of one, two and three panels, the widest routes, few and
 many random sentinels (also more than the parallel draws take, and more staged
 slots than a tile of several panels holds), every input type and width, equal scores
 across the panels, and a row that stops at the collection cap."""
@@ -29,38 +29,42 @@ def _w(n, d, dtype, k, m, r, causal=False, heads=2, kv=1, nk=0, **kw):
                         causal=causal, n_layers=3, anchor_every=0, **kw)
 
 
+# (workload, least share of rows compared).  Rows inside the tie bands are left
+# out, which the inputs alone decide (by the oracle's scores): near the boundary
+# of 4096 normal scores neighbours lie about 1 / (4096 * 0.05) = 5e-3 standard
+# deviations apart, closer in a row's own cluster; the band is 1e-4 of the score
+# plus the product's rounding bound 2 d 2^-24 sum |q k|, at two boundaries (k and
+# T).  So wide rows and wide routes lose up to four tenths, narrow ones few.
 CASES = [
-    _w(40, 128, "bf16", 64, 32, 32, nk=2049),
-    _w(33, 64, "bf16", 8, 4, 4, nk=2304),               # nine stages: five and four
-    _w(65, 128, "f32", 32, 16, 16, nk=3000),
-    _w(31, 32, "f32", 100, 28, 40, nk=4095),
-    _w(36, 256, "bf16", 20, 108, 9, nk=4096),
-    _w(34, 32, "bf16", 3, 2, 130, nk=4000, n_sink=3, n_recent=2),  # r past the parallel draws
-    _w(34, 64, "f32", 1, 0, 255, nk=2500),              # more slots than several panels stage
-    _w(2100, 128, "bf16", 64, 32, 32, causal=True, heads=1),
-    _w(4096, 32, "bf16", 16, 8, 8, causal=True, heads=1, n_sink=1, n_recent=4, min_reuse=1),
+    (_w(40, 128, "bf16", 64, 32, 32, nk=2049), 0.75),
+    (_w(33, 64, "bf16", 8, 4, 4, nk=2304), 0.9),        # nine stages: three panels of three
+    (_w(65, 128, "f32", 32, 16, 16, nk=3000), 0.75),
+    (_w(31, 32, "f32", 100, 28, 40, nk=4095), 0.75),
+    (_w(36, 256, "bf16", 20, 108, 9, nk=4096), 0.55),
+    (_w(34, 32, "bf16", 3, 2, 130, nk=4000, n_sink=3, n_recent=2), 0.95),  # r past the parallel draws
+    (_w(34, 64, "f32", 1, 0, 255, nk=2500), 0.99),      # more slots than several panels stage
+    (_w(2100, 128, "bf16", 64, 32, 32, causal=True, heads=1), 0.9),
+    (_w(4096, 32, "bf16", 16, 8, 8, causal=True, heads=1, n_sink=1, n_recent=4, min_reuse=1), 0.9),
 ]
 
 
-@pytest.mark.parametrize("w", CASES, ids=[f"n{w.n}x{w.nk}-d{w.d}-{w.dtype}-T{w.k + w.m}-r{w.r}{'-causal' if w.causal else ''}"
-                                          for w in CASES])
-def test_panels_step_parity(w):
+@pytest.mark.parametrize("w,floor", CASES, ids=[f"n{w.n}x{w.nk}-d{w.d}-{w.dtype}-T{w.k + w.m}-r{w.r}{'-causal' if w.causal else ''}"
+                                                for w, _ in CASES])
+def test_panels_step_parity(w, floor):
     from parity_util import step_compare
     print(w, flush=True)
     st = step_compare(w, note=lambda s: (print(s, flush=True), sys.stdout.flush()))
-    # Rows inside the tie bands are left out, a property of the inputs alone: near
-    # the boundary of 4096 normal scores neighbours lie about 1 / (4096 * 0.05) =
-    # 5e-3 standard deviations apart, the band is 1e-4 of the score (2 deviations)
-    # plus the product's rounding bound, at two boundaries (k and T): up to a few
-    # tenths of the rows with wide bf16 routes.
-    assert st["compared"] >= 0.5 * st["rows"]
+    assert st["compared"] >= floor * st["rows"]
 
 
-@pytest.mark.parametrize("nk,k,m,r,ones", [(4096, 90, 38, 12, False), (2500, 64, 0, 40, False), (4096, 64, 32, 8, True)])
+@pytest.mark.parametrize("nk,k,m,r,ones", [(4096, 90, 38, 12, None), (2500, 64, 0, 40, None), (4096, 64, 32, 8, "late"),
+                                           (4096, 64, 32, 8, "last")])
 def test_panels_exact_ties(nk, k, m, r, ones):
     """Small-integer inputs: every score is exact in binary32, and the boundary
-    rank falls among equal scores of both panels (`ones`: among scores that only
-    the second panel holds above the first's), lower id first."""
+    rank falls among equal scores of all three panels (4096 keys: 1536, 1536 and
+    1024 of them), lower id first.  `late`: among scores that the second and the
+    third panel hold above the first's; `last`: among the third's alone, with
+    fewer, higher ones that the list carries over from the first two."""
     from parity_util import dev, ledger_np
     from paper_2609_07306_amd import routerelay as rr
     n = 40
@@ -71,8 +75,13 @@ def test_panels_exact_ties(nk, k, m, r, ones):
     if ones:
         Q[:, 2:] = 1.0
         K[:] = 0.0
+    if ones == "late":
         K[:, 3000:, 0] = 1.0
         K[:, 3500:3530, 1] = 1.0
+    elif ones == "last":
+        K[:, 3100:, 0] = 1.0
+        K[:, 700:720, :2] = 1.0
+        K[:, 2000:2015, :3] = 1.0
     p = oracle.Problem(2, 2, n, nk, 32, k, m, r)
     led = rr.Ledger(rr.Config(2, 2, n, nk, 32, k, m, r, "bf16"))
     led.anchor(0, dev(synth.bf16_round(Q), "bf16"), dev(synth.bf16_round(K), "bf16"))
