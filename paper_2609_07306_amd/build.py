@@ -35,8 +35,9 @@ ARCH = "gfx950"
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # device code never produces or tests NaN (scores are finite, +-inf are
-    # sentinels), so min / max / med3 need no NaN canonicalisation
+    # no device code relies on what the compiler makes of a NaN (where one may be
+    # met, the resident tile's collection, it uses compare and max instructions
+    # of its own), so min / max / med3 need no NaN canonicalisation
     "-Xarch_device", "-fno-honor-nans",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

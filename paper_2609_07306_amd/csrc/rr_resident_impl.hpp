@@ -28,7 +28,7 @@
 // register spilled in the sweep is reloaded behind the keys in flight and waits
 // for them (two panels of eight stages: 7100 cycles a stage, three of six: 3400).
 // Long-context schedule (32 heads x 4096, causal, bf16, T = 96): 2653 us with the
-// two-sweep tiles, 2018 us.
+// two-sweep tiles, 2024 us.
 //
 // Selecting the T = k + m best of a row:
 //   1. bound: per lane and register slot the maximum over the stages, so a
@@ -37,10 +37,10 @@
 //      adjacent lanes per row (DPP reductions), give a v that few more than T
 //      scores reach.
 //   2. collection: a lane counts its scores >= v, takes its place in the row's
-//      list by one LDS add, and appends (score, id) in any order.  A row with more candidates than its
-//      list holds raises v by bisection on the order-preserving integer image
-//      of the scores, then cuts its ties by id: counts over registers, every
-//      wave following all 32 rows.
+//      list by one LDS add, and appends (score, id) in any order.  A row with
+//      more candidates than its list holds raises v by bisection on the
+//      order-preserving integer image of the scores, then cuts its ties by id:
+//      counts over registers, every wave following all 32 rows.
 //   3. selection, 2 NW adjacent lanes per row, the row's lanes in one wave
 //      (no barrier from here on): a bitonic network over the lanes sorts the
 //      candidates' scores for the k-th and T-th; R and N become bitmaps over
@@ -52,6 +52,10 @@
 //      Earlier slots never yield to later ones, so this ends at the draws of
 //      the slots decided one by one.
 // The results leave through LDS staging in whole 16-byte pieces per row.
+//
+// Any float is a score that a row may have: infinities rank as what they are, a
+// NaN with -inf, and the bound's overshoots (an uncut range, a rounding) only
+// cost repair steps, for each row's count is checked before its list is used.
 #pragma once
 
 #include <float.h>
@@ -582,265 +586,372 @@ void resident_kernel(RouteArgs a)
     unsigned long long fin = 0;  // relay: tiles finished before this one << 32 | their flagged rows
     if constexpr (P > 1 && MODE == MODE_RELAY) mark_ledger();
     for (int p = 0;; ++p) {
-    const bool last = P == 1 || p == np - 1;
-    if constexpr (P > 1) {
-        // (opaque: values derived from the lane are formed again in each panel
-        // instead of being kept in registers across the sweeps)
-        asm volatile("" : "+v"(tid));
-        lane = tid & 63;
-        hh = lane >> 5;
-        l32 = lane & 31;
-        lrow = lane / S::PR;
-        lcol = lane % S::PR;
-    }
-    if (P > 1 && p > 0) {
-        kp += 32 * NW * nb;
-        nb = min(nb, nbt - p * nb);
-        seg = 16 * nb;
-        kbase = kp + (2 * w + hh) * seg;
-        if (tid < 96) row_cnt[tid >> 5][tid & 31] = 0;
-        fq.load(Qrow, hh);  // (loaded again: kept, it would cost the collection its registers)
-        gload_first();
-    }
-    const unsigned char *const lp = wst + l32 * S::LS + hh * (S::RB / 2);
-    // relay: the ledger's marks (and their barrier) come under stage `mst`
-    // (several panels: before the first)
-    const int mst = P > 1 ? -1 : min(KT > 2 ? 2 : 0, nb - 1);
-    static_for<KT>([&](auto sc) __attribute__((always_inline)) {
-        constexpr int st = decltype(sc)::value;
-        if (st < nb) {
-            f32x16_t c = f32x16_t{};
-            static_for<S::SUB>([&](auto qc) __attribute__((always_inline)) {
-                constexpr int q = decltype(qc)::value, x = st * S::SUB + q;  // x: the part's number
-                constexpr int nst = (x + NF) / S::SUB, nq = (x + NF) % S::SUB;
-                lstore(breg[x % NF]);
-                if (nst < nb) gload(breg[x % NF], nst, nq);
-                wave_sync();
-                c = KeyPart<DT, D, S::SUB>::mma(lp, fq, q, c);
-                if (q == S::SUB - 1) {
-                    acc[st] = c;
-                    if constexpr (st > 0) {
-                        if (MODE != MODE_RELAY || st > mst) finish(acc[st > 0 ? st - 1 : 0], st - 1);
+        const bool last = P == 1 || p == np - 1;
+        if constexpr (P > 1) {
+            // (opaque: values derived from the lane are formed again in each panel
+            // instead of being kept in registers across the sweeps)
+            asm volatile("" : "+v"(tid));
+            lane = tid & 63;
+            hh = lane >> 5;
+            l32 = lane & 31;
+            lrow = lane / S::PR;
+            lcol = lane % S::PR;
+        }
+        if (P > 1 && p > 0) {
+            kp += 32 * NW * nb;
+            nb = min(nb, nbt - p * nb);
+            seg = 16 * nb;
+            kbase = kp + (2 * w + hh) * seg;
+            if (tid < 96) row_cnt[tid >> 5][tid & 31] = 0;
+            fq.load(Qrow, hh);  // (loaded again: kept, it would cost the collection its registers)
+            gload_first();
+        }
+        const unsigned char *const lp = wst + l32 * S::LS + hh * (S::RB / 2);
+        // relay: the ledger's marks (and their barrier) come under stage `mst`
+        // (several panels: before the first)
+        const int mst = P > 1 ? -1 : min(KT > 2 ? 2 : 0, nb - 1);
+        static_for<KT>([&](auto sc) __attribute__((always_inline)) {
+            constexpr int st = decltype(sc)::value;
+            if (st < nb) {
+                f32x16_t c = f32x16_t{};
+                static_for<S::SUB>([&](auto qc) __attribute__((always_inline)) {
+                    constexpr int q = decltype(qc)::value, x = st * S::SUB + q;  // x: the part's number
+                    constexpr int nst = (x + NF) / S::SUB, nq = (x + NF) % S::SUB;
+                    lstore(breg[x % NF]);
+                    if (nst < nb) gload(breg[x % NF], nst, nq);
+                    wave_sync();
+                    c = KeyPart<DT, D, S::SUB>::mma(lp, fq, q, c);
+                    if (q == S::SUB - 1) {
+                        acc[st] = c;
+                        if constexpr (st > 0) {
+                            if (MODE != MODE_RELAY || st > mst) finish(acc[st > 0 ? st - 1 : 0], st - 1);
+                        }
+                    }
+                    wave_sync();
+                });
+                if constexpr (P == 1 && MODE == MODE_RELAY && st <= (KT > 2 ? 2 : 0)) {
+                    if (st == mst) {
+                        mark_ledger();
+                        static_for<st>([&](auto jc) __attribute__((always_inline)) { finish(acc[decltype(jc)::value], decltype(jc)::value); });
                     }
                 }
-                wave_sync();
-            });
-            if constexpr (P == 1 && MODE == MODE_RELAY && st <= (KT > 2 ? 2 : 0)) {
-                if (st == mst) {
-                    mark_ledger();
-                    static_for<st>([&](auto jc) __attribute__((always_inline)) { finish(acc[decltype(jc)::value], decltype(jc)::value); });
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[st][i] = -INFINITY;
-        }
-    });
-    static_for<KT>([&](auto sc) __attribute__((always_inline)) {
-        constexpr int st = decltype(sc)::value;
-        if (st == nb - 1) finish(acc[st], st);
-    });
-
-    // kept maxima -> the wave's LDS rows (the key tile there is consumed)
-    {
-        float *kp = reinterpret_cast<float *>(wst) + l32 * S::KSTR + hh * 16;
-        float gm[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            gm[i] = acc[0][i];
-#pragma unroll
-            for (int st = 1; st < KT; ++st) gm[i] = fmaxf(gm[i], acc[st][i]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            reinterpret_cast<float4 *>(kp)[q] = make_float4(gm[4 * q], gm[4 * q + 1], gm[4 * q + 2], gm[4 * q + 3]);
-        if (MODE == MODE_RELAY && last) {
-            amin = fminf(amin, __shfl_xor(amin, 32, 64));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-            if (hh == 0) ab_s[w][l32] = make_float2(amin, bmax);
-        }
-    }
-    lds_barrier();
-
-    // ------------------------------------------------- trigger, bound per row
-    if constexpr (P > 1) {
-        asm volatile("" : "+v"(tid));
-        part = tid & (LPR - 1);
-        sr = w * RPW + (tid & 63) / LPR;
-        grow = g0 + min(sr, nrows - 1);
-    }
-    // (before the last panel every row counts as routed)
-    if (MODE == MODE_RELAY && last) {
-        const float2 x = ab_s[part & (NW - 1)][sr];
-        const float al = row_min<LPR>(x.x), be = row_max<LPR>(x.y);
-        int flagged = 0;
-        if (on && part == 0) {
-            const bool flag = relay_trigger(led_ns, al, be, a.gamma, a.gamma_rows, grow, a.layer,
-                                            a.min_reuse > 0 ? a.led_build[grow] : 0, a.min_reuse);
-            a.flags[grow] = flag ? 1 : 0;
-            if (a.mask_out) a.mask_out[grow] = flag ? 1 : 0;
-            a.alpha_out[grow] = al;
-            a.beta_out[grow] = be;
-            if (!flag) a.led_age[grow] = a.layer - a.led_build[grow];
-            flagged = flag ? 1 : 0;
-            const int ni = a.causal ? min(i0 + sr + 1, a.n_k) : a.n_k;
-            atomicAdd(&s_pairs, (unsigned long long)(led_nc + led_ns + (flag ? ni : 0)));
-            if (flag) atomicAdd(&s_rows, 1);
-        }
-        on = row_sum<LPR>(flagged) != 0;
-    }
-    {
-        const float4 *kp = reinterpret_cast<const float4 *>(smem + (part >> 1) * S::WST) + sr * (S::KSTR / 4) + (part & 1) * 4;
-        // a later panel takes the candidates so far as well
-        constexpr int NU = P > 1 ? 16 + S::CPL : 16;
-        const int c1 = (P > 1 && p > 0) ? row_c[sr] : 0;
-        const bool dead = P > 1 && p > 0 && c1 == 0;  // stopped at the sweep cap: keeps no candidate
-        float u[NU];
-        if constexpr (P > 1) {
-            const uint2 *lst = reinterpret_cast<const uint2 *>(lists + sr * S::LSTR);
-#pragma unroll
-            for (int j = 0; j < S::CPL; ++j) {
-                u[16 + j] = -INFINITY;
-                if (part + LPR * j < c1) u[16 + j] = __uint_as_float(lst[part + LPR * j].x);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 x = kp[q];
-            u[4 * q] = x.x;
-            u[4 * q + 1] = x.y;
-            u[4 * q + 2] = x.z;
-            u[4 * q + 3] = x.w;
-        }
-        float rmax = u[0], umin = INFINITY;
-        int nfin = 0;
-#pragma unroll
-        for (int q = 0; q < NU; ++q) {
-            const bool fin = u[q] > -INFINITY;
-            rmax = fmaxf(rmax, u[q]);
-            umin = fminf(umin, fin ? u[q] : INFINITY);
-            nfin += fin ? 1 : 0;
-        }
-        rmax = row_max<LPR>(rmax);
-        umin = row_min<LPR>(umin);
-        nfin = row_sum<LPR>(nfin);
-        const int T = a.k + a.m;
-        // The T-th maximum to one of 127 levels of [lo, hi]: the maxima become
-        // bytes, four to a word, and a level's count takes three operations a
-        // word (subtract, top bits, population count); seven steps give the
-        // highest level that T of them reach.  A level holds the maxima within
-        // half a step of it however the conversion rounds, so its bound lies
-        // 0.51 steps below.  Where much of the row falls into one level (an
-        // outlier stretches the range) that level is cut again.  A range whose
-        // width or its reciprocal leaves the normal floats is not cut: its
-        // levels would come out as infinities and NaN.  lo then stays where it
-        // is, a lower bound still, and the collection raises it.
-        float lo = nfin >= T ? umin : kLowest, hi = rmax;
-        if (P > 1 && p > 0) {
-            const uint32_t before = th_s[sr];
-            if (before < kStopped) lo = fmaxf(lo, __uint_as_float(before));
-        }
-        int clo = nfin;
-        for (int it = 0; it < kBoundRounds; ++it) {
-            const float span = hi - lo;
-            const bool go = on & (nfin >= T) & (clo > T + (T >> 3)) & (span > kLeastSpan) & (span < kMostSpan);
-            if (__ballot(go) == 0ull) break;
-            const float step = span * (1.0f / 127.0f), inv = 127.0f * __builtin_amdgcn_rcpf(span);
-            uint32_t x[NU / 4];
-#pragma unroll
-            for (int q = 0; q < NU / 4; ++q) {
-                uint32_t b = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    b = __builtin_amdgcn_cvt_pk_u8_f32(fminf((u[4 * q + e] - lo) * inv, 127.0f), e, b);
-                x[q] = b | 0x80808080u;
-            }
-            uint32_t lev = 0;  // the level in every byte
-            int cl = clo;
-#pragma unroll
-            for (uint32_t b = 0x40404040u; b >= 0x01010101u; b >>= 1) {
-                const uint32_t p = lev | b;
-                int n = 0;
-#pragma unroll
-                for (int q = 0; q < NU / 4; ++q) n += __popc((x[q] - p) & 0x80808080u);
-                n = row_sum<LPR>(n);
-                lev = n >= T ? p : lev;
-                cl = n >= T ? n : cl;
-            }
-            const float L = (float)(lev & 0x7Fu);
-            if (go) {
-                hi = lo + (L + 0.51f) * step;
-                if (lev != 0u) lo = lo + (L - 0.51f) * step;
-                clo = (lev == 0u && it > 0) ? T : cl;
-            }
-        }
-        if (part == 0) {
-            th_s[sr] = on ? (dead ? kStopped : __float_as_uint(lo)) : kNotRouted;
-            rmax_s[sr] = rmax;
-        }
-    }
-    lds_barrier();
-    if (MODE == MODE_RELAY && last) {
-        if (tid == 0)
-            pub = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.done) + 1, s_pairs, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-    }
-
-    // ------------------------------------------- collection into row lists
-    // (every wave follows all 32 rows: lane (l32, hh) holds row l32's state)
-    // (the threshold is kept as bits: kNoScore must not meet float arithmetic)
-    uint32_t th = th_s[l32];
-    bool live = th < kStopped;  // the row collects
-    routed = th != kNotRouted;
-    th = live ? th : kNoScore;
-    const int nv = last ? myn : min(myn, kp + 32 * NW * nb);  // the row's valid keys so far
-    int base = 0, cnt = 0;
-    {
-        int th_id = INT_MAX, state = 0, id_lo = -1, id_hi = 0;  // state 1: cutting ties at th by id
-        uint32_t lk = float_order(__uint_as_float(th)), hk = float_order(rmax_s[l32]) + 1u;
-        bool settled = true, ties = false;
-        int total = 0;
-        // the candidates so far, rewritten with this panel's: every 2 NW-th is this lane's
-        constexpr int NX = P > 1 ? S::CPL : 1;
-        float xs[NX];
-        uint32_t xi[NX];
-        const bool more_lists = P > 1 && p > 0;
-        if constexpr (P > 1) {
-            const int c1 = p > 0 ? row_c[l32] : 0;
-            const uint2 *lst = reinterpret_cast<const uint2 *>(lists + l32 * S::LSTR);
-#pragma unroll
-            for (int j = 0; j < NX; ++j) {
-                const int e = 2 * w + hh + LPR * j;
-                xs[j] = -INFINITY;
-                xi[j] = INT_MAX;  // (past every id cut)
-                if (e < c1) {
-                    const uint2 x = lst[e];
-                    xs[j] = __uint_as_float(x.x);
-                    xi[j] = x.y;
-                }
-            }
-        }
-        // ties: a score is admitted above tf, or at it by its id (none of a row that does not collect)
-        auto tie_score = [&]() { return __uint_as_float(live ? th : 0x7F800000u); };
-        auto tie_cut = [&]() { return live ? th_id : -1; };
-        for (int it = 0;; ++it) {
-            cnt = 0;
-            if (!ties) {
-                Count4 c4;
-                if constexpr (P > 1) {
-                    if (more_lists) c4.template add<NX>(xs, th);
-                }
-#pragma unroll
-                for (int st = 0; st < KT; ++st) {
-                    if (st < nb) c4.add(acc[st], th);  // (masked scores are -inf, th is above)
-                }
-                cnt += c4.sum();
             } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[st][i] = -INFINITY;
+            }
+        });
+        static_for<KT>([&](auto sc) __attribute__((always_inline)) {
+            constexpr int st = decltype(sc)::value;
+            if (st == nb - 1) finish(acc[st], st);
+        });
+
+        // kept maxima -> the wave's LDS rows (the key tile there is consumed)
+        {
+            float *const kept = reinterpret_cast<float *>(wst) + l32 * S::KSTR + hh * 16;
+            float gm[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                gm[i] = acc[0][i];
+#pragma unroll
+                for (int st = 1; st < KT; ++st) gm[i] = fmaxf(gm[i], acc[st][i]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                reinterpret_cast<float4 *>(kept)[q] = make_float4(gm[4 * q], gm[4 * q + 1], gm[4 * q + 2], gm[4 * q + 3]);
+            if (MODE == MODE_RELAY && last) {
+                amin = fminf(amin, __shfl_xor(amin, 32, 64));
+                bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+                if (hh == 0) ab_s[w][l32] = make_float2(amin, bmax);
+            }
+        }
+        lds_barrier();
+
+        // ------------------------------------------------- trigger, bound per row
+        if constexpr (P > 1) {
+            asm volatile("" : "+v"(tid));
+            part = tid & (LPR - 1);
+            sr = w * RPW + (tid & 63) / LPR;
+            grow = g0 + min(sr, nrows - 1);
+        }
+        // (before the last panel every row counts as routed)
+        if (MODE == MODE_RELAY && last) {
+            const float2 x = ab_s[part & (NW - 1)][sr];
+            const float al = row_min<LPR>(x.x), be = row_max<LPR>(x.y);
+            int flagged = 0;
+            if (on && part == 0) {
+                const bool flag = relay_trigger(led_ns, al, be, a.gamma, a.gamma_rows, grow, a.layer,
+                                                a.min_reuse > 0 ? a.led_build[grow] : 0, a.min_reuse);
+                a.flags[grow] = flag ? 1 : 0;
+                if (a.mask_out) a.mask_out[grow] = flag ? 1 : 0;
+                a.alpha_out[grow] = al;
+                a.beta_out[grow] = be;
+                if (!flag) a.led_age[grow] = a.layer - a.led_build[grow];
+                flagged = flag ? 1 : 0;
+                const int ni = a.causal ? min(i0 + sr + 1, a.n_k) : a.n_k;
+                atomicAdd(&s_pairs, (unsigned long long)(led_nc + led_ns + (flag ? ni : 0)));
+                if (flag) atomicAdd(&s_rows, 1);
+            }
+            on = row_sum<LPR>(flagged) != 0;
+        }
+        {
+            const float4 *const kept = reinterpret_cast<const float4 *>(smem + (part >> 1) * S::WST) + sr * (S::KSTR / 4) + (part & 1) * 4;
+            // a later panel takes the candidates so far as well
+            constexpr int NU = P > 1 ? 16 + S::CPL : 16;
+            const int c1 = (P > 1 && p > 0) ? row_c[sr] : 0;
+            const bool dead = P > 1 && p > 0 && c1 == 0;  // stopped at the sweep cap: keeps no candidate
+            float u[NU];
+            if constexpr (P > 1) {
+                const uint2 *lst = reinterpret_cast<const uint2 *>(lists + sr * S::LSTR);
+#pragma unroll
+                for (int j = 0; j < S::CPL; ++j) {
+                    u[16 + j] = -INFINITY;
+                    if (part + LPR * j < c1) u[16 + j] = __uint_as_float(lst[part + LPR * j].x);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 x = kept[q];
+                u[4 * q] = x.x;
+                u[4 * q + 1] = x.y;
+                u[4 * q + 2] = x.z;
+                u[4 * q + 3] = x.w;
+            }
+            float rmax = u[0], umin = INFINITY;
+            int nfin = 0;
+#pragma unroll
+            for (int q = 0; q < NU; ++q) {
+                const bool fin = u[q] > -INFINITY;
+                rmax = fmaxf(rmax, u[q]);
+                umin = fminf(umin, fin ? u[q] : INFINITY);
+                nfin += fin ? 1 : 0;
+            }
+            rmax = row_max<LPR>(rmax);
+            umin = row_min<LPR>(umin);
+            nfin = row_sum<LPR>(nfin);
+            const int T = a.k + a.m;
+            // The T-th maximum to one of 127 levels of [lo, hi]: the maxima become
+            // bytes, four to a word, and a level's count takes three operations a
+            // word (subtract, top bits, population count); seven steps give the
+            // highest level that T of them reach.  A level holds the maxima within
+            // half a step of it however the conversion rounds, so its bound lies
+            // 0.51 steps below.  Where much of the row falls into one level (an
+            // outlier stretches the range) that level is cut again.  A range whose
+            // width or its reciprocal leaves the normal floats is not cut: its
+            // levels would come out as infinities and NaN.  lo then stays where it
+            // is, a lower bound still, and the collection raises it.
+            float lo = nfin >= T ? umin : kLowest, hi = rmax;
+            if (P > 1 && p > 0) {
+                const uint32_t before = th_s[sr];
+                if (before < kStopped) lo = fmaxf(lo, __uint_as_float(before));
+            }
+            int clo = nfin;
+            for (int it = 0; it < kBoundRounds; ++it) {
+                const float span = hi - lo;
+                const bool go = on & (nfin >= T) & (clo > T + (T >> 3)) & (span > kLeastSpan) & (span < kMostSpan);
+                if (__ballot(go) == 0ull) break;
+                const float step = span * (1.0f / 127.0f), inv = 127.0f * __builtin_amdgcn_rcpf(span);
+                uint32_t x[NU / 4];
+#pragma unroll
+                for (int q = 0; q < NU / 4; ++q) {
+                    uint32_t b = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        b = __builtin_amdgcn_cvt_pk_u8_f32(fminf((u[4 * q + e] - lo) * inv, 127.0f), e, b);
+                    x[q] = b | 0x80808080u;
+                }
+                uint32_t lev = 0;  // the level in every byte
+                int cl = clo;
+#pragma unroll
+                for (uint32_t b = 0x40404040u; b >= 0x01010101u; b >>= 1) {
+                    const uint32_t p = lev | b;
+                    int n = 0;
+#pragma unroll
+                    for (int q = 0; q < NU / 4; ++q) n += __popc((x[q] - p) & 0x80808080u);
+                    n = row_sum<LPR>(n);
+                    lev = n >= T ? p : lev;
+                    cl = n >= T ? n : cl;
+                }
+                const float L = (float)(lev & 0x7Fu);
+                if (go) {
+                    hi = lo + (L + 0.51f) * step;
+                    if (lev != 0u) lo = lo + (L - 0.51f) * step;
+                    clo = (lev == 0u && it > 0) ? T : cl;
+                }
+            }
+            if (part == 0) {
+                th_s[sr] = on ? (dead ? kStopped : __float_as_uint(lo)) : kNotRouted;
+                rmax_s[sr] = rmax;
+            }
+        }
+        lds_barrier();
+        if (MODE == MODE_RELAY && last) {
+            if (tid == 0)
+                pub = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.done) + 1, s_pairs, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        }
+
+        // ------------------------------------------- collection into row lists
+        // (every wave follows all 32 rows: lane (l32, hh) holds row l32's state)
+        // (the threshold is kept as bits: kNoScore must not meet float arithmetic)
+        uint32_t th = th_s[l32];
+        bool live = th < kStopped;  // the row collects
+        routed = th != kNotRouted;
+        th = live ? th : kNoScore;
+        const int nv = last ? myn : min(myn, kp + 32 * NW * nb);  // the row's valid keys so far
+        int base = 0, cnt = 0;
+        {
+            int th_id = INT_MAX, state = 0, id_lo = -1, id_hi = 0;  // state 1: cutting ties at th by id
+            uint32_t lk = float_order(__uint_as_float(th)), hk = float_order(rmax_s[l32]) + 1u;
+            bool settled = true, ties = false;
+            int total = 0;
+            // the candidates so far, rewritten with this panel's: every 2 NW-th is this lane's
+            constexpr int NX = P > 1 ? S::CPL : 1;
+            float xs[NX];
+            uint32_t xi[NX];
+            const bool more_lists = P > 1 && p > 0;
+            if constexpr (P > 1) {
+                const int c1 = p > 0 ? row_c[l32] : 0;
+                const uint2 *lst = reinterpret_cast<const uint2 *>(lists + l32 * S::LSTR);
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    const int e = 2 * w + hh + LPR * j;
+                    xs[j] = -INFINITY;
+                    xi[j] = INT_MAX;  // (past every id cut)
+                    if (e < c1) {
+                        const uint2 x = lst[e];
+                        xs[j] = __uint_as_float(x.x);
+                        xi[j] = x.y;
+                    }
+                }
+            }
+            // ties: a score is admitted above tf, or at it by its id (none of a row that does not collect)
+            auto tie_score = [&]() { return __uint_as_float(live ? th : 0x7F800000u); };
+            auto tie_cut = [&]() { return live ? th_id : -1; };
+            for (int it = 0;; ++it) {
+                cnt = 0;
+                if (!ties) {
+                    Count4 c4;
+                    if constexpr (P > 1) {
+                        if (more_lists) c4.template add<NX>(xs, th);
+                    }
+#pragma unroll
+                    for (int st = 0; st < KT; ++st) {
+                        if (st < nb) c4.add(acc[st], th);  // (masked scores are -inf, th is above)
+                    }
+                    cnt += c4.sum();
+                } else {
+                    const float tf = tie_score();
+                    const int tid_cut = tie_cut();
+                    if (more_lists) {
+#pragma unroll
+                        for (int j = 0; j < NX; ++j) cnt += ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) ? 1 : 0;
+                    }
+#pragma unroll
+                    for (int st = 0; st < KT; ++st) {
+                        if (st < nb) {
+                            const int lim = tid_cut - (kbase + 16 * st);
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) {
+                                const float x = no_nan(acc[st][i]);
+                                cnt += ((x > tf) | ((x == tf) & (i <= lim))) ? 1 : 0;
+                            }
+                        }
+                    }
+                }
+                const int slot = it % 3;
+                if (cnt > 0) base = atomicAdd(&row_cnt[slot][l32], cnt);
+                if (it > 0 && tid < 32) row_cnt[(it + 1) % 3][tid] = 0;
+                lds_barrier();
+                total = row_cnt[slot][l32];
+                bool again = false;
+                // the row's least admissible count (T_i <= T; rows not routed admit nothing)
+                bool few = false;
+                if (it == 0) {
+                    few = live & (total < min(a.k + a.m, nv));
+                    if (__ballot((total > CAP) | few) == 0ull) break;  // the usual case
+                    // the bound's rounding overshot, or the row has fewer finite scores
+                    // than it takes
+                    if (few) lk = float_order(-INFINITY);
+                }
+                if (live) {
+                    const int ki = a.k_rows ? min(max(a.k_rows[g0 + min(l32, nrows - 1)], 1), a.k) : a.k;
+                    const int Ti = ki + a.m, need = min(Ti, nv);
+                    if (state == 1) {
+                        const int mid = th_id;
+                        if (total >= need)
+                            id_hi = mid;
+                        else
+                            id_lo = mid;
+                        if (id_hi - id_lo > 1) {
+                            th_id = id_lo + ((id_hi - id_lo) >> 1);
+                            again = true;
+                        } else if (mid != id_hi) {
+                            th_id = id_hi;
+                            again = true;
+                        }
+                    } else if (total < need) {
+                        hk = float_order(__uint_as_float(th));
+                        again = true;
+                    } else if (total > CAP) {
+                        lk = float_order(__uint_as_float(th));
+                        again = true;
+                    }
+                    if (state == 0 && again) {
+                        if (hk - lk > 1u) {
+                            th = few ? __float_as_uint(kLowest) : __float_as_uint(order_float(lk + ((hk - lk) >> 1)));
+                        } else {
+                            // lk is the T_i-th score: the chunks above it and the
+                            // lowest ids of its ties; bisect the id cut.  (Ties at
+                            // -inf: the masked keys' ids lie past the valid ones.)
+                            state = 1;
+                            th = __float_as_uint(order_float(lk));
+                            id_lo = -1;
+                            id_hi = nv - 1;
+                            th_id = -1 + (nv >> 1);
+                        }
+                    }
+                }
+                const uint64_t more = __ballot(again);
+                if (more == 0ull) break;
+                if (it + 1 >= a.sweep_cap) {
+                    // stopped at the cap: the row keeps no candidate
+                    settled = !again;
+                    if (again) {
+                        live = false;
+                        th = kNoScore;
+                        cnt = 0;
+                        total = 0;
+                    }
+                    break;
+                }
+                ties = __ballot(state == 1) != 0ull;
+            }
+            if (w == 0 && hh == 0) {
+                row_c[l32] = total;
+                if (!settled && a.unconverged) atomicAdd(a.unconverged, 1ull);
+            }
+            if (!ties) {
+                uint32_t at = (uint32_t)(l32 * S::LSTR + base * 8) + lds_offset(lists);
+                if constexpr (P > 1) {
+                    if (p > 0) append_listed<NX>(xs, xi, th, at);
+                }
+                static_for<KT>([&](auto sc) __attribute__((always_inline)) {
+                    constexpr int st = decltype(sc)::value;
+                    if (st < nb) append16(acc[st], th, at, (uint32_t)(kbase + 16 * st));
+                });
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            } else {
+                uint2 *lst = reinterpret_cast<uint2 *>(lists + l32 * S::LSTR) + base;
                 const float tf = tie_score();
                 const int tid_cut = tie_cut();
                 if (more_lists) {
 #pragma unroll
-                    for (int j = 0; j < NX; ++j) cnt += ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) ? 1 : 0;
+                    for (int j = 0; j < NX; ++j) {
+                        if ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) {
+                            *lst = make_uint2(__float_as_uint(xs[j]), xi[j]);
+                            ++lst;
+                        }
+                    }
                 }
 #pragma unroll
                 for (int st = 0; st < KT; ++st) {
@@ -849,132 +960,25 @@ void resident_kernel(RouteArgs a)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) {
                             const float x = no_nan(acc[st][i]);
-                            cnt += ((x > tf) | ((x == tf) & (i <= lim))) ? 1 : 0;
-                        }
-                    }
-                }
-            }
-            const int slot = it % 3;
-            if (cnt > 0) base = atomicAdd(&row_cnt[slot][l32], cnt);
-            if (it > 0 && tid < 32) row_cnt[(it + 1) % 3][tid] = 0;
-            lds_barrier();
-            total = row_cnt[slot][l32];
-            bool again = false;
-            // the row's least admissible count (T_i <= T; rows not routed admit nothing)
-            bool few = false;
-            if (it == 0) {
-                few = live & (total < min(a.k + a.m, nv));
-                if (__ballot((total > CAP) | few) == 0ull) break;  // the usual case
-                // the bound's rounding overshot, or the row has fewer finite scores
-                // than it takes
-                if (few) lk = float_order(-INFINITY);
-            }
-            if (live) {
-                const int ki = a.k_rows ? min(max(a.k_rows[g0 + min(l32, nrows - 1)], 1), a.k) : a.k;
-                const int Ti = ki + a.m, need = min(Ti, nv);
-                if (state == 1) {
-                    const int mid = th_id;
-                    if (total >= need)
-                        id_hi = mid;
-                    else
-                        id_lo = mid;
-                    if (id_hi - id_lo > 1) {
-                        th_id = id_lo + ((id_hi - id_lo) >> 1);
-                        again = true;
-                    } else if (mid != id_hi) {
-                        th_id = id_hi;
-                        again = true;
-                    }
-                } else if (total < need) {
-                    hk = float_order(__uint_as_float(th));
-                    again = true;
-                } else if (total > CAP) {
-                    lk = float_order(__uint_as_float(th));
-                    again = true;
-                }
-                if (state == 0 && again) {
-                    if (hk - lk > 1u) {
-                        th = few ? __float_as_uint(kLowest) : __float_as_uint(order_float(lk + ((hk - lk) >> 1)));
-                    } else {
-                        // lk is the T_i-th score: the chunks above it and the
-                        // lowest ids of its ties; bisect the id cut.  (Ties at
-                        // -inf: the masked keys' ids lie past the valid ones.)
-                        state = 1;
-                        th = __float_as_uint(order_float(lk));
-                        id_lo = -1;
-                        id_hi = nv - 1;
-                        th_id = -1 + (nv >> 1);
-                    }
-                }
-            }
-            const uint64_t more = __ballot(again);
-            if (more == 0ull) break;
-            if (it + 1 >= a.sweep_cap) {
-                // stopped at the cap: the row keeps no candidate
-                settled = !again;
-                if (again) {
-                    live = false;
-                    th = kNoScore;
-                    cnt = 0;
-                    total = 0;
-                }
-                break;
-            }
-            ties = __ballot(state == 1) != 0ull;
-        }
-        if (w == 0 && hh == 0) {
-            row_c[l32] = total;
-            if (!settled && a.unconverged) atomicAdd(a.unconverged, 1ull);
-        }
-        if (!ties) {
-            uint32_t at = (uint32_t)(l32 * S::LSTR + base * 8) + lds_offset(lists);
-            if constexpr (P > 1) {
-                if (p > 0) append_listed<NX>(xs, xi, th, at);
-            }
-            static_for<KT>([&](auto sc) __attribute__((always_inline)) {
-                constexpr int st = decltype(sc)::value;
-                if (st < nb) append16(acc[st], th, at, (uint32_t)(kbase + 16 * st));
-            });
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        } else {
-            uint2 *lst = reinterpret_cast<uint2 *>(lists + l32 * S::LSTR) + base;
-            const float tf = tie_score();
-            const int tid_cut = tie_cut();
-            if (more_lists) {
-#pragma unroll
-                for (int j = 0; j < NX; ++j) {
-                    if ((xs[j] > tf) | ((xs[j] == tf) & ((int)xi[j] <= tid_cut))) {
-                        *lst = make_uint2(__float_as_uint(xs[j]), xi[j]);
-                        ++lst;
-                    }
-                }
-            }
-#pragma unroll
-            for (int st = 0; st < KT; ++st) {
-                if (st < nb) {
-                    const int lim = tid_cut - (kbase + 16 * st);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float x = no_nan(acc[st][i]);
-                        if ((x > tf) | ((x == tf) & (i <= lim))) {
-                            *lst = make_uint2(__float_as_uint(x), (uint32_t)(kbase + 16 * st + i));
-                            ++lst;
+                            if ((x > tf) | ((x == tf) & (i <= lim))) {
+                                *lst = make_uint2(__float_as_uint(x), (uint32_t)(kbase + 16 * st + i));
+                                ++lst;
+                            }
                         }
                     }
                 }
             }
         }
-    }
-    if (MODE == MODE_RELAY && last) {
-        // published after the pair total has been added (pub has returned)
-        if (tid == 0) {
-            asm volatile("" : "+v"(pub)::"memory");
-            fin = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.done),
-                                         (1ull << 32) + (unsigned long long)(uint32_t)s_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (MODE == MODE_RELAY && last) {
+            // published after the pair total has been added (pub has returned)
+            if (tid == 0) {
+                asm volatile("" : "+v"(pub)::"memory");
+                fin = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.done),
+                                             (1ull << 32) + (unsigned long long)(uint32_t)s_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
-    }
-    lds_barrier();
-    if (last) break;
+        lds_barrier();
+        if (last) break;
     }
 
     // -------------------------------------------- selection (row's own lanes)
@@ -1263,14 +1267,15 @@ void resident_kernel(RouteArgs a)
                                 }
                             }
                             pend |= hit;
-                        } else
-                        for (int j = 0; LPR * j < a.r; ++j) {  // (uniform)
-                            const int s = part + LPR * j;
-                            if (go & (s < a.r) & (((pend >> j) & 1u) == 0u)) {
-                                const int z = dr[s], v = claim[z];
-                                if (v < s) pend |= 1u << j;
-                                if (v > s) claim[z] = (uint8_t)s;
-                                again |= v > s;
+                        } else {
+                            for (int j = 0; LPR * j < a.r; ++j) {  // (uniform)
+                                const int s = part + LPR * j;
+                                if (go & (s < a.r) & (((pend >> j) & 1u) == 0u)) {
+                                    const int z = dr[s], v = claim[z];
+                                    if (v < s) pend |= 1u << j;
+                                    if (v > s) claim[z] = (uint8_t)s;
+                                    again |= v > s;
+                                }
                             }
                         }
                         if (out) pend = 0u;
