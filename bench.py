@@ -46,10 +46,10 @@ PEAK = {"hbm": 8000.0, "mfma_bf16": 2500.0, "mfma_f32": 157.3}  # GB/s, TFLOP/s
 # HBM bytes per launch of the dominant kernel, from byte-counter passes
 # (FETCH_SIZE, WRITE_SIZE, calibrated on a copy of known size) recorded in
 # this profile; valid only while the kernel's sources hash to the recorded value.
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "route_rescore_scale_n1024_hbm_bytes.md")
-TRAFFIC_SOURCES = ["paper_2609_07306_amd/csrc/rr_route_impl.hpp", "paper_2609_07306_amd/csrc/rr_device.hpp",
-                   "paper_2609_07306_amd/csrc/rr_internal.hpp", "paper_2609_07306_amd/csrc/rr_route_bf16_reroute.hip",
-                   "paper_2609_07306_amd/build.py"]
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "resident_scale_n1024_hbm_bytes.md")
+TRAFFIC_SOURCES = ["paper_2609_07306_amd/csrc/rr_resident_impl.hpp", "paper_2609_07306_amd/csrc/rr_resident_inst.hip",
+                   "paper_2609_07306_amd/csrc/rr_route_impl.hpp", "paper_2609_07306_amd/csrc/rr_device.hpp",
+                   "paper_2609_07306_amd/csrc/rr_internal.hpp", "paper_2609_07306_amd/build.py"]
 
 
 def recorded_traffic(kernel: str):
