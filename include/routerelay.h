@@ -22,11 +22,10 @@
  *   - A route is a SET, stored sorted by ascending chunk id and padded with
  *     -1 (a row with n_i < k routes to all of its valid chunks).  Ties in
  *     score are broken toward the lower chunk id; -0 equals +0.
- *   - Scores may be any finite float or +inf.  Where fewer than k + m of a
- *     row's scores lie above -inf, and for NaN, the route is as above with NaN
- *     as -inf by the tiles that keep their scores in registers (see the
- *     options), and may come short (-1) by the others; the ids handed out are
- *     valid chunks of the row either way.
+ *   - Scores may be any finite float or infinity.  The tiles that keep their
+ *     scores in registers (see the options) rank a NaN with -inf; the two-sweep
+ *     tiles must not meet one, and may leave the route of a row short (-1)
+ *     where fewer than k + m of its scores lie above -inf.
  *   - Every call enqueues work on the given HIP stream (NULL: the null
  *     stream) and returns; outputs, including device counters, are valid once
  *     that stream has reached the enqueued work.  No call synchronises the
