@@ -22,10 +22,9 @@
  *   - A route is a SET, stored sorted by ascending chunk id and padded with
  *     -1 (a row with n_i < k routes to all of its valid chunks).  Ties in
  *     score are broken toward the lower chunk id; -0 equals +0.
- *   - Scores may be any finite float or infinity.  The tiles that keep their
- *     scores in registers (see the options) rank a NaN with -inf; the two-sweep
- *     tiles must not meet one, and may leave the route of a row short (-1)
- *     where fewer than k + m of its scores lie above -inf.
+ *   - Scores may be any finite float or infinity.  A NaN ranks with -inf in the
+ *     tiles that keep their scores in registers (see the options); the two-sweep
+ *     tiles must not meet one.
  *   - Every call enqueues work on the given HIP stream (NULL: the null
  *     stream) and returns; outputs, including device counters, are valid once
  *     that stream has reached the enqueued work.  No call synchronises the

@@ -583,7 +583,8 @@ __device__ __forceinline__ void bound_of_kept(const float *us, int tid, int T, f
 // Collection-sweep epilogue: the lane appends the scores of its segment that
 // reach its row's threshold to its sub-list.  A chunk is admitted when
 // s > th, or s == th and its id is at most th_id; th_id is INT_MAX except
-// in a tie cut, so the wave normally takes the one-compare path.  Appends
+// in a tie cut, and th is -inf only in rows with fewer than T scores above it,
+// so the wave normally takes the one-compare path.  Appends
 // past the sub-list's capacity run on into the row's later sub-lists, never
 // past the row's dummy slot: a row with a sub-list over capacity is swept
 // again with new placements, which rewrite all of its sub-lists, so the
@@ -607,8 +608,9 @@ struct CollectEpi {
     }
 
     // put(s >= th, s, key) with the test taken from the sign of s - th
-    // (exact; a -inf threshold admits every score, +inf none): integer
-    // arithmetic on the sign mask, no compare results to wait for
+    // (exact for th > -inf, which a score of -inf reaches too, and a +inf
+    // threshold admits no finite score): integer arithmetic on the sign mask,
+    // no compare results to wait for
     __device__ __forceinline__ void put_ge(float s, int key)
     {
         const uint32_t below = (uint32_t)((int32_t)__float_as_uint(s - th) >> 31);  // all ones when s < th
@@ -624,7 +626,7 @@ struct CollectEpi {
     {
         const int k0 = sbase + 16 * st;  // this lane's keys: k0 .. k0 + 15
         next = tile_product(fq, fk);
-        if (full && __ballot(th_id - k0 < 15) == 0ull) {
+        if (full && __ballot((th_id - k0 < 15) | (th == -INFINITY)) == 0ull) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) put_ge(acc[i], k0 + i);
             interleave_mfma<F::NS, (16 * 7 + F::NS - 1) / F::NS>();

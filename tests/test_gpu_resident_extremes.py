@@ -1,6 +1,7 @@
 """Scores at the ends of binary32 through the resident-score route kernel, one
 panel of keys and several: zeros of both signs, NaN, ranges wider than the
-largest float, infinities.
+largest float, infinities; past 4096 keys the two-sweep tiles and the split
+relay (without NaN).
 
 The inputs are scaled unit vectors or constants, so that every score is known
 exactly; the expected routes are the k highest scores, -0 equal to +0, ties to
@@ -108,7 +109,7 @@ def _queries(n, q):
     return Q
 
 
-@pytest.mark.parametrize("nk", [100, 600, 2304])
+@pytest.mark.parametrize("nk", [100, 600, 2304, 4200])
 def test_finite_scores_wider_than_the_largest_float(nk):
     """Rows whose highest and lowest scores lie further apart than the largest
     finite float, the highest T close together or not."""
@@ -123,7 +124,7 @@ def test_finite_scores_wider_than_the_largest_float(nk):
     _check_routing(Q, K, s, k, m, r)
 
 
-@pytest.mark.parametrize("nk,hot", [(100, 50), (600, 45), (600, 500), (2304, 60), (2304, 1500)])
+@pytest.mark.parametrize("nk,hot", [(100, 50), (600, 45), (600, 500), (2304, 60), (2304, 1500), (4200, 60), (4200, 2500)])
 def test_infinite_scores(nk, hot):
     """Products that overflow to +inf: as many as a row selects and more, in a
     row's list or past it, beside rows where the same chunks are finite."""
@@ -138,7 +139,7 @@ def test_infinite_scores(nk, hot):
     _check_routing(Q, K, s, k, m, r)
 
 
-@pytest.mark.parametrize("nk,finite", [(100, 20), (600, 0), (600, 39), (2304, 5), (4096, 0)])
+@pytest.mark.parametrize("nk,finite", [(100, 20), (600, 0), (600, 39), (2304, 5), (4096, 0), (4200, 0), (4200, 36)])
 def test_valid_chunks_of_minus_infinity(nk, finite):
     """Rows with fewer finite scores than they select (products that overflow to
     -inf) take the lowest ids of the others, beside rows of finite scores."""
@@ -153,7 +154,7 @@ def test_valid_chunks_of_minus_infinity(nk, finite):
     _check_routing(Q, K, s, k, m, r)
 
 
-@pytest.mark.parametrize("n", [300, 2200])
+@pytest.mark.parametrize("n", [300, 2200, 4200])
 def test_minus_infinity_under_the_causal_mask(n):
     """... and never a chunk past the row's position, which the mask also gives -inf."""
     from paper_2609_07306_amd import routerelay as rr
